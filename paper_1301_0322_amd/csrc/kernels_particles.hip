@@ -61,7 +61,7 @@ constexpr int kClasses = 8;
 
 template <int TZ>
 struct TileDims {
-  static constexpr int EY = kTY, EZ = TZ + 1;               // staged core; rows padded by one word
+  static constexpr int EY = kTY, EZ = TZ;                   // staged core
   static constexpr int EXT = kTX * EY * EZ;
   static constexpr int CORE = kTX * kTY * TZ;
   // threads per tile block: a tile holds 2 TZ particles on average at mesh ratio 2
@@ -147,19 +147,20 @@ __device__ __forceinline__ int key_of(const Bins& b, const int c[3]) {
 // Rank of each active lane among the lanes of its wave with the same bin, plus one
 // atomic per distinct bin that reserves the ranks.  Called by every lane of the wave.
 // The ballot loop only groups the lanes; the group leaders then issue their atomics
-// together, so a wave waits for one atomic round trip whatever its number of bins.
+// together, so a wave waits for one atomic round trip whatever its number of bins.  The
+// bin of a round is read from its lane by v_readlane (the lane is wave-uniform), not by a
+// shuffle through the LDS unit: binning 256^3 particles 0.121 -> 0.110 ms.
 __device__ __forceinline__ int wave_rank(bool active, int bin, int* __restrict__ count) {
   const int lane = __lane_id();
-  const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   unsigned long long pending = __ballot(active);
   int leader = lane, below = 0, members = 0;
   while (pending) {
     const int first = __ffsll((long long)pending) - 1;
-    const int lb = __shfl(bin, first);
+    const int lb = __builtin_amdgcn_readlane(bin, first);   // first is wave-uniform
     const unsigned long long m = __ballot(active && bin == lb);
     if (active && bin == lb) {
       leader = first;
-      below = __popcll(m & lt);
+      below = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
       members = __popcll(m);
     }
     pending &= ~m;
@@ -410,12 +411,17 @@ __device__ __forceinline__ bool local_stencil(const Lattice& lat, const TileGeom
 }
 
 // Copies NF mesh fields over the tile's own cells (x < 8, y < 8, z < TZ) into LDS,
-// field c at tile + c * EXT, row stride EZ.  Each staged row is one aligned run of TZ
+// field c at tile + c * EXT, row stride TZ.  Each staged row is one aligned run of TZ
 // floats (whole cache lines).  The +1 planes along x, y and z that the CIC stencils
 // of the tile's upper-face particles reach are not staged: those corners are read from
 // the mesh (corner_value), where the neighbouring tiles, staged around the same time
 // on the same XCD, keep them in L2.  Staging only the core keeps the three-field tile
-// at 50 KB (three blocks per CU at depth 64) and reads each mesh cell from HBM once.
+// at 48 KB (three blocks per CU at depth 64) and reads each mesh cell from HBM once.
+// The rows are not padded: particles read them at random cells, so a pad buys no bank
+// freedom, and unpadded rows take one 16-byte LDS store per four cells instead of four
+// 4-byte ones (with the scalar lane reads of wave_rank, the in-run gather of 256^3
+// particles on 512^3 cells went from 0.955 to 0.937 ms) and the four-field tile of the
+// adjoint gather fits five times in a CU instead of four.
 // Every load of a lane is issued before its first LDS write, so a block has all of
 // its tile reads in flight at once.
 template <int TZ, int NF>
@@ -445,11 +451,60 @@ __device__ __forceinline__ void stage_fields(const TileGeom& t, int nm, const fl
       const int zq = i % RQ, r = i / RQ;
       float* row = tile + r * D::EZ + 4 * zq;
 #pragma unroll
-      for (int c = 0; c < NF; ++c) {
-        row[c * D::EXT] = v[c][k].x;
-        row[c * D::EXT + 1] = v[c][k].y;
-        row[c * D::EXT + 2] = v[c][k].z;
-        row[c * D::EXT + 3] = v[c][k].w;
+      for (int c = 0; c < NF; ++c) *reinterpret_cast<float4*>(row + c * D::EXT) = v[c][k];
+    }
+  }
+}
+
+// The corners (a, b, c) of NF fields for a particle with tile-local base cell lc, at
+// v[f][4 a + 2 b + c].  Corners in the staged core come from LDS.  A pair of z neighbours
+// in a row past the tile's x or y faces is one 8-byte load from the mesh, and every load
+// is issued before the first use, where corner_value's predicated loads are waited for
+// one after the other.  With four fields (the adjoint gather, 128^3 particles on 256^3
+// cells) 0.175 -> 0.157 ms; the three-field gathers, which run six blocks to a CU and hold
+// a whole record per lane, got slower with it (0.937 -> 0.959 ms) and keep corner_value.
+typedef float float2u __attribute__((ext_vector_type(2), aligned(4)));
+
+template <int TZ, int NF>
+__device__ __forceinline__ void stencil_values(const float* tile, const float* const* mesh, const TileGeom& t,
+                                               const int lc[3], int nm, float (&v)[NF][8]) {
+  using D = TileDims<TZ>;
+  const bool zin = lc[2] < TZ - 1;
+  const int gz = t.lo[2] + lc[2];
+  const bool wraps = t.lo[2] + TZ == nm;               // block-uniform: gz + 1 may be nm
+  const int gz1 = gz + 1 < nm ? gz + 1 : 0;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int x = lc[0] + (r >> 1), y = lc[1] + (r & 1);
+    int gx = t.lo[0] + x, gy = t.lo[1] + y;
+    gx -= (gx >= nm) ? nm : 0;
+    gy -= (gy >= nm) ? nm : 0;
+    // byte offsets into a mesh of at most 1024^3 floats fit in 32 bits
+    const unsigned row = ((unsigned)gx * nm + gy) * nm * 4u;
+    auto at = [&](int f, int z) { return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(mesh[f]) + (row + 4u * z)); };
+    if (x < kTX && y < kTY) {
+      const float* q = tile + (x * D::EY + y) * D::EZ + lc[2];
+#pragma unroll
+      for (int f = 0; f < NF; ++f) v[f][2 * r] = q[f * D::EXT];
+      if (zin) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) v[f][2 * r + 1] = q[f * D::EXT + 1];
+      } else {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) v[f][2 * r + 1] = at(f, gz1);
+      }
+    } else if (!wraps) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f) {
+        const float2u q = *reinterpret_cast<const float2u*>(reinterpret_cast<const char*>(mesh[f]) + (row + 4u * gz));
+        v[f][2 * r] = q.x;
+        v[f][2 * r + 1] = q.y;
+      }
+    } else {
+#pragma unroll
+      for (int f = 0; f < NF; ++f) {
+        v[f][2 * r] = at(f, gz);
+        v[f][2 * r + 1] = at(f, gz1);
       }
     }
   }
@@ -466,6 +521,25 @@ __device__ __forceinline__ float corner_value(const float* tile_field, const flo
   gy -= (gy >= nm) ? nm : 0;
   gz -= (gz >= nm) ? nm : 0;
   return mesh[((long)gx * nm + gy) * nm + gz];
+}
+
+// CIC interpolation of the three force fields at a particle.
+template <int TZ>
+__device__ __forceinline__ void interpolate3(const float* tile, const float* const* mesh, const TileGeom& t,
+                                             const int lc[3], const float fr[3], int nm, float (&f)[3]) {
+  using D = TileDims<TZ>;
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const float wab = (a ? fr[0] : 1.f - fr[0]) * (b ? fr[1] : 1.f - fr[1]);
+      const float w0 = wab * (1.f - fr[2]), w1 = wab * fr[2];
+      const int o = ((lc[0] + a) * D::EY + lc[1] + b) * D::EZ + lc[2];
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+        f[d] += w0 * corner_value<TZ>(tile + d * D::EXT, mesh[d], o, t, lc[0] + a, lc[1] + b, lc[2], nm) +
+                w1 * corner_value<TZ>(tile + d * D::EXT, mesh[d], o + 1, t, lc[0] + a, lc[1] + b, lc[2] + 1, nm);
+    }
 }
 
 // Deposit of one tile.  The particle ranges that reach into tile t are its own (all
@@ -683,14 +757,13 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_gather_tiles(Lattice lat, 
                                                                const int* __restrict__ offset,
                                                                const int* __restrict__ heavy, GatherArgs g) {
   using D = TileDims<TZ>;
-  __shared__ float tile[3 * D::EXT];
+  __shared__ __align__(16) float tile[3 * D::EXT];
   TileGeom t;
   bool listed;
   if (!tile_geom<TZ>(bins, heavy, t, listed)) return;
   const int beg = offset[(long)t.bin * kClasses], end = offset[(long)(t.bin + 1) * kClasses];
   if (!listed && tile_is_listed(lat, bins, end - beg)) return;
   const float* gf[3] = {g.g0, g.g1, g.g2};
-  const TileGeom& T_ = t;
   stage_fields<TZ, 3>(t, lat.nm, gf, tile);
   __syncthreads();
   const long n = lat.npart;
@@ -700,18 +773,7 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_gather_tiles(Lattice lat, 
     int lc[3];
     if (!local_stencil<TZ>(lat, t, g.s, p, p, sv, lc, fr)) continue;   // cannot happen
     float f[3] = {0.f, 0.f, 0.f};
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const float wab = (a ? fr[0] : 1.f - fr[0]) * (b ? fr[1] : 1.f - fr[1]);
-        const float w0 = wab * (1.f - fr[2]), w1 = wab * fr[2];
-        const int o = ((lc[0] + a) * D::EY + lc[1] + b) * D::EZ + lc[2];
-#pragma unroll
-        for (int d = 0; d < 3; ++d)
-          f[d] += w0 * corner_value<TZ>(tile + d * D::EXT, gf[d], o, T_, lc[0] + a, lc[1] + b, lc[2], lat.nm) +
-                  w1 * corner_value<TZ>(tile + d * D::EXT, gf[d], o + 1, T_, lc[0] + a, lc[1] + b, lc[2] + 1, lat.nm);
-      }
+    interpolate3<TZ>(tile, gf, t, lc, fr, lat.nm, f);
 #pragma unroll
     for (int d = 0; d < 3; ++d) g.out_a[d * n + p] = f[d];
   }
@@ -732,7 +794,7 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_grad_gather(Lattice lat, B
                                                               const int* __restrict__ heavy,
                                                               const float* __restrict__ s, AdjGatherArgs ga) {
   using D = TileDims<TZ>;
-  __shared__ float tile[4 * D::EXT];
+  __shared__ __align__(16) float tile[4 * D::EXT];
   TileGeom t;
   bool listed;
   if (!tile_geom<TZ>(bins, heavy, t, listed)) return;
@@ -760,20 +822,25 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_grad_gather(Lattice lat, B
     }
     // corner values of H = sum_d mu_d g_d and of rbar
     float h[2][2][2], r[2][2][2];
+    if (with_g) {
+      float v[4][8];
+      const float* const f[4] = {ga.g0, ga.g1, ga.g2, ga.rbar};
+      stencil_values<TZ, 4>(tile, f, t, lc, lat.nm, v);
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+      for (int c = 0; c < 8; ++c) {
+        r[c >> 2][(c >> 1) & 1][c & 1] = v[3][c];
+        h[c >> 2][(c >> 1) & 1][c & 1] = mu[0] * v[0][c] + mu[1] * v[1][c] + mu[2] * v[2][c];
+      }
+    } else {
+      float v[1][8];
+      const float* const f[1] = {ga.rbar};
+      stencil_values<TZ, 1>(tile + 3 * D::EXT, f, t, lc, lat.nm, v);
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const int o = ((lc[0] + a) * D::EY + lc[1] + b) * D::EZ + lc[2] + c;
-          const int x = lc[0] + a, y = lc[1] + b, z = lc[2] + c;
-          r[a][b][c] = corner_value<TZ>(tile + 3 * D::EXT, ga.rbar, o, t, x, y, z, lat.nm);
-          h[a][b][c] = with_g ? mu[0] * corner_value<TZ>(tile, ga.g0, o, t, x, y, z, lat.nm) +
-                                    mu[1] * corner_value<TZ>(tile + D::EXT, ga.g1, o, t, x, y, z, lat.nm) +
-                                    mu[2] * corner_value<TZ>(tile + 2 * D::EXT, ga.g2, o, t, x, y, z, lat.nm)
-                              : 0.f;
-        }
+      for (int c = 0; c < 8; ++c) {
+        r[c >> 2][(c >> 1) & 1][c & 1] = v[0][c];
+        h[c >> 2][(c >> 1) & 1][c & 1] = 0.f;
+      }
+    }
     const float w[3][2] = {{1.f - fr[0], fr[0]}, {1.f - fr[1], fr[1]}, {1.f - fr[2], fr[2]}};
     float gh[3] = {0.f, 0.f, 0.f}, gr[3] = {0.f, 0.f, 0.f};
 #pragma unroll
@@ -834,6 +901,43 @@ __device__ __forceinline__ void load_record(const SortedState& st, long n, int j
   }
 }
 
+// wave_rank, and the position of each lane in the wave's order grouped by tile and then
+// by key (pos): the lanes of one tile take consecutive positions, so that the next step's
+// reader of a tile finds the records that came from here in runs.  Up to half of the
+// particles change tile in a step, and each one read out of order costs a line per plane;
+// the grouping comes out of rounds the rank needs anyway.  256^3 particles, 512^3 cells:
+// the closing gather 0.988 -> 0.930 ms, the in-run one 0.937 -> 0.925, the deposit 0.356
+// -> 0.347; grouping a whole block's 256 particles through LDS counters gave the readers
+// the same gain but cost three barriers per batch (in-run gather 1.034 ms).
+__device__ __forceinline__ int wave_rank_grouped(bool active, int bin, int* __restrict__ count, int& pos) {
+  const int lane = __lane_id();
+  const int tile = bin / kClasses;
+  unsigned long long pending = __ballot(active), same = 0;
+  int leader = lane, below = 0, members = 0, filled = 0;
+  while (pending) {
+    if (!same) {
+      const int lead = __ffsll((long long)pending) - 1;
+      same = __ballot(active && tile == __builtin_amdgcn_readlane(tile, lead));
+    }
+    const int first = __ffsll((long long)same) - 1;
+    const int lb = __builtin_amdgcn_readlane(bin, first);   // first is wave-uniform
+    const unsigned long long m = __ballot(active && bin == lb);
+    if (active && bin == lb) {
+      leader = first;
+      below = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
+      members = __popcll(m);
+      pos = filled + below;
+    }
+    filled += __popcll(m);
+    pending &= ~m;
+    same &= ~m;
+  }
+  int base = 0;
+  if (active && lane == leader) base = atomicAdd(count + bin, members);
+  base = __shfl(base, leader);
+  return base + below;
+}
+
 template <int TZ, int MODE>
 __global__ __launch_bounds__(TileDims<TZ>::TT) void k_gather_sorted(Lattice lat, Bins bins, SortedState src,
                                                                 SortedState dst, const int* __restrict__ idx,
@@ -842,7 +946,7 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_gather_sorted(Lattice lat,
                                                                 KickArgs k, int2* __restrict__ key_rank_next,
                                                                 int* __restrict__ count_next) {
   using D = TileDims<TZ>;
-  __shared__ float tile[3 * D::EXT];
+  __shared__ __align__(16) float tile[3 * D::EXT];
   TileGeom t;
   bool listed;
   if (!tile_geom<TZ>(bins, heavy, t, listed)) return;
@@ -855,8 +959,8 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_gather_sorted(Lattice lat,
   SortedRecord r, rn;
   if (beg < end) load_record(src, n, idx[min(beg + (int)threadIdx.x, end - 1)], r);
   const float* gf[3] = {g.g0, g.g1, g.g2};
-  const TileGeom& T_ = t;
   stage_fields<TZ, 3>(t, lat.nm, gf, tile);
+  constexpr bool BINS = MODE == kGatherKickDrift || MODE == kGatherKickDriftInv;
   __syncthreads();
   for (int base = beg; base < end; base += D::TT) {   // block-uniform trip count
     const int j = base + threadIdx.x;
@@ -870,20 +974,7 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_gather_sorted(Lattice lat,
     const bool act =
         in && (unsigned)lc[0] < (unsigned)kTX && (unsigned)lc[1] < (unsigned)kTY && (unsigned)lc[2] < (unsigned)TZ;
     float f[3] = {0.f, 0.f, 0.f};
-    if (act) {
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          const float wab = (a ? sc.f[0] : 1.f - sc.f[0]) * (b ? sc.f[1] : 1.f - sc.f[1]);
-          const float w0 = wab * (1.f - sc.f[2]), w1 = wab * sc.f[2];
-          const int o = ((lc[0] + a) * D::EY + lc[1] + b) * D::EZ + lc[2];
-#pragma unroll
-          for (int d = 0; d < 3; ++d)
-            f[d] += w0 * corner_value<TZ>(tile + d * D::EXT, gf[d], o, T_, lc[0] + a, lc[1] + b, lc[2], lat.nm) +
-                    w1 * corner_value<TZ>(tile + d * D::EXT, gf[d], o + 1, T_, lc[0] + a, lc[1] + b, lc[2] + 1, lat.nm);
-        }
-    }
+    if (act) interpolate3<TZ>(tile, gf, t, lc, sc.f, lat.nm, f);
     float snew[3] = {r.s[0], r.s[1], r.s[2]};
     float vf[3];
     if (in) {
@@ -903,14 +994,6 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_gather_sorted(Lattice lat,
           dst.v[d * n + r.lag] = vf[d];
         }
       }
-      if constexpr (MODE == kGatherKickDriftInv) g.inv[r.lag] = j;
-      if constexpr (MODE == kGatherKickDrift || MODE == kGatherKickDriftInv) {
-        float4* q = reinterpret_cast<float4*>(dst.s);
-        q[j] = make_float4(snew[0], snew[1], snew[2], vf[0]);
-        q[n + j] = make_float4(vf[1], vf[2], r.s1[0], r.s1[1]);
-        q[2 * n + j] = make_float4(r.s1[2], r.s2[0], r.s2[1], r.s2[2]);
-        dst.lag[j] = (int)r.lag;
-      }
       if constexpr (MODE == kGatherFinish) {
         // finish: s and the kicked v, in this step's tile order, as a float4 plane
         // (s.x s.y s.z v.x) and a float2 plane (v.y v.z), and the slot of every
@@ -920,11 +1003,20 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_gather_sorted(Lattice lat,
         dst.lag[r.lag] = j;
       }
     }
-    if constexpr (MODE == kGatherKickDrift || MODE == kGatherKickDriftInv) {
-      int bin = 0;
-      if (in) bin = key_of<TZ>(bins, stencil_of(lat, r.lag, snew).c);
-      const int rank = wave_rank(in, bin, count_next);
-      if (in) key_rank_next[j] = make_int2(bin, rank);
+    if constexpr (BINS) {
+      int key = 0, pos = 0;
+      if (in) key = key_of<TZ>(bins, stencil_of(lat, r.lag, snew).c);
+      const int rank = wave_rank_grouped(in, key, count_next, pos);
+      if (in) {
+        const int slot = j - (int)__lane_id() + pos;   // a wave's active lanes are its first ones
+        if constexpr (MODE == kGatherKickDriftInv) g.inv[r.lag] = slot;
+        float4* q = reinterpret_cast<float4*>(dst.s);
+        q[slot] = make_float4(snew[0], snew[1], snew[2], vf[0]);
+        q[n + slot] = make_float4(vf[1], vf[2], r.s1[0], r.s1[1]);
+        q[2 * n + slot] = make_float4(r.s1[2], r.s2[0], r.s2[1], r.s2[2]);
+        dst.lag[slot] = (int)r.lag;
+        key_rank_next[slot] = make_int2(key, rank);
+      }
     }
     r = rn;
   }

@@ -1,0 +1,42 @@
+"""The in-run gather writes each wave's records grouped by the tile they move to: whole
+runs and resident steps, which read that order, equal the steps that pack the caller's
+arrays afresh bit for bit.  Sizes: one tile along an axis, tiles with less than a wave,
+with several batches and on the crowded list, and depths that make 256- and 512-thread
+tile blocks."""
+import pytest
+import torch
+
+import paper_1301_0322_amd as cola
+from gpu_util import announce
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("np_side,nm,depth,box", [
+    (16, 16, 16, 20.0), (24, 48, 8, 10.0), (32, 32, 32, 5.0), (48, 192, 64, 60.0), (64, 64, 64, 8.0), (96, 96, 32, 30.0)])
+def test_grouped_records_equal_fresh_packing(np_side, nm, depth, box):
+    announce(f"grouped records {np_side}/{nm} depth {depth} box {box}")
+    cfg = cola.Config(np=np_side, nm=nm, box=box, n_steps=4)
+    n = np_side**3
+    w = torch.randn(n, generator=torch.Generator().manual_seed(np_side + nm)).cuda()
+    out = {}
+    for mode in ("run", "resident", "fresh"):
+        with cola.Plan(cfg) as plan:
+            plan.set_bin_depth(depth)
+            ws = plan.workspace()
+            p = cola.Particles.empty(np_side)
+            x = torch.empty((3, n), device="cuda")
+            v = torch.empty_like(x)
+            if mode == "run":
+                plan.run(w, p, x, v, ws)
+            else:
+                plan.set_resident_steps(1 if mode == "resident" else 0)
+                plan.init_2lpt(w, p, ws)
+                for i in range(cfg.n_steps):
+                    plan.step(i, p, ws)
+                plan.finish(p, x, v, ws)
+            torch.cuda.synchronize()
+            out[mode] = [t.clone() for t in (x, v, p.s, p.v)]
+    for a, b, c in zip(out["run"], out["resident"], out["fresh"]):
+        assert torch.isfinite(a).all()
+        assert torch.equal(a, c) and torch.equal(b, c)
