@@ -186,11 +186,21 @@ __global__ __launch_bounds__(kPartThreads) void k_bin_count(Lattice lat, Bins bi
   if (ok) key_rank[p] = make_int2(bin, rank);
 }
 
-// Exclusive scan of count[0..n) into offset[0..n] (offset[n] = total) in three
-// launches: chunk sums, a one-block scan of the chunk sums, and the chunk scans.
-// The first launch also clears count_next (the counts the next gather fills).
+// Exclusive scan of count[0..n) into offset[0..n] (offset[n] = total), and the list of
+// crowded tiles: every tile holding more than heavy_min particles (own classes) is
+// appended to heavy[1..] (count in heavy[0]).  With heavy_min = ceil(npart / cap) fewer
+// than cap tiles can qualify, so the list never overflows.  The order within the list
+// does not matter: each tile's result is independent of when it runs.  count_next (the
+// counts the next gather fills) is cleared on the way.
+// Two launches: sums of 4096-key chunks, then every chunk's scan, whose block adds up the
+// sums before its own (at most 4096 of them) instead of waiting for a launch that scans
+// them; a thread pair holds one tile's eight keys, so the crowded tiles need no pass of
+// their own.  Every launch here is a few microseconds of latency: sums, their scan, the
+// chunk scans and the tile list took 19 us in four launches at nm = 512.  Up to kScanOne
+// keys (nm = 128 at depth 32) one block does it all in one launch.
 constexpr int kScanThreads = 1024;
 constexpr int kScanChunk = 4 * kScanThreads;
+constexpr int kScanOne = 2 * kScanChunk;
 
 __device__ __forceinline__ int block_sum_1024(int v, int* wsum) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -226,74 +236,72 @@ __device__ __forceinline__ int block_scan_1024(int v, int* wsum, int& total) {
   return carry + inc - v;
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_sums(const int* __restrict__ count, int n,
-                                                            int* __restrict__ part, int* __restrict__ count_next,
-                                                            int n_pad) {
-  __shared__ int wsum[kScanThreads / 64];
-  const long base = (long)blockIdx.x * kScanChunk;
-  int v = 0;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const long i = base + threadIdx.x + k * kScanThreads;
-    if (i < n) v += count[i];
+// One chunk: keys base .. base + 3 of this thread (n is a multiple of 8), `carry` the keys
+// before the chunk; appends the chunk's crowded tiles through slot(); returns the total.
+template <class Slot>
+__device__ __forceinline__ int scan_chunk(const int* __restrict__ count, int n, long base, int carry, int* wsum,
+                                          int* __restrict__ offset, int heavy_min, int* __restrict__ heavy,
+                                          Slot&& slot) {
+  const bool in = base < n;
+  const int4 v = in ? *reinterpret_cast<const int4*>(count + base) : make_int4(0, 0, 0, 0);
+  const int s4 = v.x + v.y + v.z + v.w;
+  const int tile = s4 + __shfl_xor(s4, 1);
+  int total;
+  const int run = carry + block_scan_1024(s4, wsum, total);
+  if (in) {
+    const int r1 = run + v.x, r2 = r1 + v.y;
+    *reinterpret_cast<int4*>(offset + base) = make_int4(run, r1, r2, r2 + v.z);
+    if (threadIdx.x % 2 == 0 && tile > heavy_min) heavy[1 + slot()] = (int)(base / kClasses);
   }
-  const int t = block_sum_1024(v, wsum);
-  if (threadIdx.x == 0) part[blockIdx.x] = t;
-  if (count_next)
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const long i = base + threadIdx.x + k * kScanThreads;
-      if (i < n_pad) count_next[i] = 0;
-    }
+  return total;
 }
 
-// One block: exclusive scan of the nb chunk sums in place; total to *tot.
-__global__ __launch_bounds__(kScanThreads) void k_scan_top(int* __restrict__ part, int nb, int* __restrict__ tot,
-                                                           int* __restrict__ heavy) {
+__global__ __launch_bounds__(kScanThreads) void k_scan_sums(const int* __restrict__ count, int n,
+                                                            int* __restrict__ part, int* __restrict__ count_next,
+                                                            int n_pad, int* __restrict__ heavy) {
   __shared__ int wsum[kScanThreads / 64];
-  if (threadIdx.x == 0) heavy[0] = 0;   // k_heavy_tiles appends after the offsets are final
-  int carry = 0;
-  for (int c = 0; c < nb; c += kScanThreads) {
-    const int i = c + threadIdx.x;
-    const int v = i < nb ? part[i] : 0;
-    int total;
-    const int ex = block_scan_1024(v, wsum, total);
-    if (i < nb) part[i] = carry + ex;
-    carry += total;
-    __syncthreads();   // wsum is reused by the next round
-  }
-  if (threadIdx.x == 0) *tot = carry;
+  const long base = (long)blockIdx.x * kScanChunk + 4 * threadIdx.x;
+  const int4 c = base < n ? *reinterpret_cast<const int4*>(count + base) : make_int4(0, 0, 0, 0);
+  const int t = block_sum_1024(c.x + c.y + c.z + c.w, wsum);
+  if (threadIdx.x == 0) part[blockIdx.x] = t;
+  if (count_next && base < n_pad) *reinterpret_cast<int4*>(count_next + base) = make_int4(0, 0, 0, 0);
+  if (blockIdx.x == 0 && threadIdx.x == 0) heavy[0] = 0;   // k_scan_chunks appends
 }
 
 __global__ __launch_bounds__(kScanThreads) void k_scan_chunks(const int* __restrict__ count, int n,
                                                               const int* __restrict__ part,
-                                                              int* __restrict__ offset) {
-  __shared__ int wsum[kScanThreads / 64];
+                                                              int* __restrict__ offset, int heavy_min,
+                                                              int* __restrict__ heavy) {
+  __shared__ int wsum[kScanThreads / 64], psum[kScanThreads / 64];
+  int before = 0;
+  for (int i = threadIdx.x; i < (int)blockIdx.x; i += kScanThreads) before += part[i];
+  const int carry = block_sum_1024(before, psum);
   const long base = (long)blockIdx.x * kScanChunk + 4 * threadIdx.x;
-  int v[4], s4 = 0;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    v[k] = (base + k < n) ? count[base + k] : 0;
-    s4 += v[k];
-  }
-  int total;
-  int run = part[blockIdx.x] + block_scan_1024(s4, wsum, total);
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    if (base + k < n) offset[base + k] = run;
-    run += v[k];
-  }
+  const int total =
+      scan_chunk(count, n, base, carry, wsum, offset, heavy_min, heavy, [&] { return atomicAdd(heavy, 1); });
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) offset[n] = carry + total;
 }
 
-// Crowded tiles: every tile holding more than heavy_min particles (own classes) is
-// appended to heavy[1..] (count in heavy[0]).  With heavy_min = ceil(npart / cap)
-// fewer than cap tiles can qualify, so the list never overflows.  The order within the
-// list does not matter: each tile's result is independent of when it runs.
-__global__ __launch_bounds__(kPartThreads) void k_heavy_tiles(long nbins, const int* __restrict__ offset, int heavy_min,
-                                                              int* __restrict__ heavy) {
-  const long t = (long)blockIdx.x * kPartThreads + threadIdx.x;
-  if (t >= nbins) return;
-  if (offset[(t + 1) * kClasses] - offset[t * kClasses] > heavy_min) heavy[1 + atomicAdd(heavy, 1)] = (int)t;
+__global__ __launch_bounds__(kScanThreads) void k_scan_one(const int* __restrict__ count, int n,
+                                                           int* __restrict__ count_next, int n_pad,
+                                                           int* __restrict__ offset, int heavy_min,
+                                                           int* __restrict__ heavy) {
+  __shared__ int wsum[kScanThreads / 64], listed;
+  if (threadIdx.x == 0) listed = 0;
+  __syncthreads();
+  int carry = 0;
+  for (int c = 0; c < n; c += kScanChunk) {
+    carry += scan_chunk(count, n, c + 4 * threadIdx.x, carry, wsum, offset, heavy_min, heavy,
+                        [&] { return atomicAdd(&listed, 1); });
+    __syncthreads();   // wsum is reused by the next round
+  }
+  if (count_next)
+    for (int i = 4 * threadIdx.x; i < n_pad; i += kScanChunk)
+      *reinterpret_cast<int4*>(count_next + i) = make_int4(0, 0, 0, 0);
+  if (threadIdx.x == 0) {
+    offset[n] = carry;
+    heavy[0] = listed;
+  }
 }
 
 __global__ __launch_bounds__(kPartThreads) void k_bin_scatter(long npart, const int2* __restrict__ key_rank,
@@ -338,7 +346,7 @@ struct TileGeom {
 };
 
 // Tile of this block.  The first b.heavy_cap blocks take the crowded tiles listed
-// by k_heavy_tiles (blocks past the list's length exit), so the tiles whose blocks
+// by the scan (blocks past the list's length exit), so the tiles whose blocks
 // loop over many particle batches start first instead of trailing the grid.  The
 // other blocks (virtual index v = block - heavy_cap, with v % 8 the block's XCD) map
 // v to a tile: each XCD takes the slab of tile planes bx in [k nbx/8, (k+1) nbx/8)
@@ -388,7 +396,7 @@ __device__ __forceinline__ bool tile_geom(const Bins& b, const int* heavy, TileG
 }
 
 // Whether a tile with `own` particles (its own classes) is on the crowded list: the
-// same test as k_heavy_tiles.
+// same test as the scan's.
 __device__ __forceinline__ bool tile_is_listed(const Lattice& lat, const Bins& b, int own) {
   return own > heavy_min_of(lat.npart, b.heavy_cap);
 }
@@ -1148,14 +1156,17 @@ hipError_t launch_bin_count(Lattice lat, Bins b, const float* s, BinBuffers bb, 
 }
 
 hipError_t launch_bin_scan(Bins b, BinBuffers bb, bool clear_next, hipStream_t st) {
-  const int n = (int)b.nkeys;
+  const int n = (int)b.nkeys, pad = (int)bb.count_len, heavy_min = heavy_min_of(bb.npart, b.heavy_cap);
+  int* next = clear_next ? bb.count_next : nullptr;
+  if (n <= kScanOne) {
+    hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanThreads), 0, st, bb.count, n, next, pad, bb.offset, heavy_min,
+                       bb.heavy);
+    return hipGetLastError();
+  }
   const unsigned nb = (unsigned)scan_chunks(b);
-  hipLaunchKernelGGL(k_scan_sums, dim3(nb), dim3(kScanThreads), 0, st, bb.count, n, bb.part,
-                     clear_next ? bb.count_next : nullptr, (int)bb.count_len);
-  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanThreads), 0, st, bb.part, (int)nb, bb.offset + n, bb.heavy);
-  hipLaunchKernelGGL(k_scan_chunks, dim3(nb), dim3(kScanThreads), 0, st, bb.count, n, bb.part, bb.offset);
-  hipLaunchKernelGGL(k_heavy_tiles, dim3((unsigned)((b.nbins + kPartThreads - 1) / kPartThreads)), dim3(kPartThreads), 0,
-                     st, b.nbins, bb.offset, heavy_min_of(bb.npart, b.heavy_cap), bb.heavy);
+  hipLaunchKernelGGL(k_scan_sums, dim3(nb), dim3(kScanThreads), 0, st, bb.count, n, bb.part, next, pad, bb.heavy);
+  hipLaunchKernelGGL(k_scan_chunks, dim3(nb), dim3(kScanThreads), 0, st, bb.count, n, bb.part, bb.offset, heavy_min,
+                     bb.heavy);
   return hipGetLastError();
 }
 
