@@ -259,6 +259,8 @@ int deposit_into(cola_plan p, const float* s, float* rho, float* ws, hipStream_t
   return deposit_with(p, s, rho, bin_buffers(p, ws), st);
 }
 
+constexpr int kMergeInverse = 256;   // largest mesh whose inverse passes share launches (fft_force)
+
 // Poisson solve on the density in ws mesh 0: g_d = (3/2) Om a irfft(i k_d delta_k / k^2),
 // d = 0..2, left in ws meshes 0, 1, 2 as real nm^3 fields (mesh 3 is scratch).
 int fft_force(cola_plan p, double a, float* ws, hipStream_t st) {
@@ -269,7 +271,7 @@ int fft_force(cola_plan p, double a, float* ws, hipStream_t st) {
   float* g2 = ws + 2 * r;
   const float2* tw = p->d_tw_nm;
   COLA_HIP(traced(p, kStZFwd, st,
-                  [&] { return launch_zfwd(n, g0, reinterpret_cast<float2*>(g0), (long)n * n, tw, st); }));
+                  [&] { return launch_zfwd(n, fields({g0}), fields({g0}), 1, (long)n * n, tw, st); }));
   // The y pass walks the rows the z pass wrote last first, and each force field goes
   // through its y and z inverse passes back to back (the z pass again walking
   // backwards), so those passes start on data still held by the memory-side cache.
@@ -292,6 +294,22 @@ int fft_force(cola_plan p, double a, float* ws, hipStream_t st) {
   e.scale = 1.0f;
   e.reverse = 1;
   const int h = n / 2;
+  // Up to nm = 256 the four meshes (268 MB) about fit the memory-side cache whatever the
+  // order, and short passes pay for their launches and tails: one launch runs the three y
+  // passes and one the three z passes (nm = 64: 16.1 -> 8.5 us for the inverse passes of a
+  // force, nm = 256: 137 -> 126 us).  Larger meshes keep the order below.
+  if (n <= kMergeInverse) {
+    COLA_HIP(traced(p, kStYInvPair, st, [&] {
+      return launch_col_pair(n, reinterpret_cast<const float2*>(g3), reinterpret_cast<float2*>(g2),
+                             reinterpret_cast<float2*>(g1), n, (long)n * h, h, h, tw, width_for(p, n, 0), rot, st, 0,
+                             reinterpret_cast<float2*>(g0));
+    }));
+    e.reverse = 0;
+    e.deriv = 4;   // field 2 (g2): the z component
+    return hip_status(traced(p, kStZInv, st, [&] {
+      return launch_zinv(n, fields({g0, g1, g2}), fields({g0, g1, g2}), 3, (long)n * n, tw, kEpiStore, e, st);
+    }));
+  }
   // the y pass reads the tail the x pass wrote last first; the z pass then takes
   // both of its outputs together from their heads
   COLA_HIP(traced(p, kStYInvPair, st, [&] {
@@ -573,10 +591,9 @@ int bin_only(cola_plan p, const float* s, float* ws, hipStream_t st) {
 
 // z and y forward passes over nf real fields of an n^3 grid, in place.
 int fwd_zy(cola_plan p, int stage, int n, std::initializer_list<float*> f, const float2* tw, hipStream_t st) {
-  for (float* x : f)
-    COLA_HIP(traced(p, stage, st,
-                    [&] { return launch_zfwd(n, x, reinterpret_cast<float2*>(x), (long)n * n, tw, st); }));
-  return ypass(p, stage, n, -1, fields(f), (int)f.size(), tw, st, rot_for(p, n));
+  const FieldPtrs fp = fields(f);
+  COLA_HIP(traced(p, stage, st, [&] { return launch_zfwd(n, fp, fp, (int)f.size(), (long)n * n, tw, st); }));
+  return ypass(p, stage, n, -1, fp, (int)f.size(), tw, st, rot_for(p, n));
 }
 
 // y and z inverse passes of one field, in place (scale 1).
@@ -670,7 +687,7 @@ int run_adjoint(cola_plan p, const float* w, const float* ckpt, const float* dL_
   float* sc[10];
   for (int k = 0; k < 10; ++k) sc[k] = L.lpt + k * n;
   COLA_HIP(traced(p, kStAdjLpt, st,
-                  [&] { return launch_zfwd(np_, w, reinterpret_cast<float2*>(sc[9]), (long)np_ * np_, twp, st); }));
+                  [&] { return launch_zfwd(np_, fields({const_cast<float*>(w)}), fields({sc[9]}), 1, (long)np_ * np_, twp, st); }));
   const int rot_p = rot_for(p, np_);
   COLA_TRY(ypass(p, kStAdjLpt, np_, -1, fields({sc[9]}), 1, twp, st, rot_p));
   MulArgs ml{};
@@ -837,7 +854,7 @@ int cola_init_2lpt(cola_plan p, const float* w, const cola_particles* q, void* w
   const float2* tw = p->d_tw_np;
   // delta_k and its derivatives: s1 into q->s1, Hessian into q->s and q->v.
   COLA_HIP(traced(p, kStLptZFwd, st,
-                  [&] { return launch_zfwd(n, w, reinterpret_cast<float2*>(w0), (long)n * n, tw, st); }));
+                  [&] { return launch_zfwd(n, fields({const_cast<float*>(w)}), fields({w0}), 1, (long)n * n, tw, st); }));
   const int rot = rot_for(p, n);
   COLA_TRY(ypass(p, kStLptYFwd, n, -1, fields({w0}), 1, tw, st, rot));
   MulArgs m{};
@@ -861,7 +878,7 @@ int cola_init_2lpt(cola_plan p, const float* w, const cola_particles* q, void* w
   }));
   // second order: s2_k = -i k S_k / k^2
   COLA_HIP(traced(p, kStLptZFwd, st,
-                  [&] { return launch_zfwd(n, w0, reinterpret_cast<float2*>(w0), (long)n * n, tw, st); }));
+                  [&] { return launch_zfwd(n, fields({w0}), fields({w0}), 1, (long)n * n, tw, st); }));
   COLA_TRY(ypass(p, kStLptYFwd, n, -1, fields({w0}), 1, tw, st, rot));
   float* s2[3] = {q->s2, q->s2 + r, q->s2 + 2 * r};
   FieldPtrs f_s2 = fields({s2[0], s2[1], s2[2]});
@@ -899,7 +916,7 @@ int fft_forward(cola_plan p, float* g, hipStream_t st) {
   const long h = n / 2;
   const float2* tw = p->d_tw_nm;
   COLA_HIP(traced(p, kStZFwd, st,
-                  [&] { return launch_zfwd(n, g, reinterpret_cast<float2*>(g), (long)n * n, tw, st); }));
+                  [&] { return launch_zfwd(n, fields({g}), fields({g}), 1, (long)n * n, tw, st); }));
   COLA_TRY(ypass(p, kStYFwd, n, -1, fields({g}), 1, tw, st, 0));
   // x: columns along x (stride n h) in tiles of kz at fixed y
   return hip_status(traced(p, kStAnalysis, st, [&] {
@@ -1066,7 +1083,7 @@ int cola_fft_r2c(cola_plan p, int32_t n, const float* in, float* out, void* stre
   hipStream_t st = (hipStream_t)stream;
   const float2* tw = twiddle_for(p, n);
   COLA_HIP(traced(p, kStFft, st,
-                  [&] { return launch_zfwd(n, in, reinterpret_cast<float2*>(out), (long)n * n, tw, st); }));
+                  [&] { return launch_zfwd(n, fields({const_cast<float*>(in)}), fields({out}), 1, (long)n * n, tw, st); }));
   COLA_TRY(ypass(p, kStFft, n, -1, fields({out}), 1, tw, st, 0));
   const long h = n / 2;
   FieldPtrs f = fields({out});

@@ -50,9 +50,10 @@ struct EpiArgs {
 
 bool fft_size_supported(int n);
 
-// Forward real-to-complex z pass: rows of n reals -> rows of n/2 complex
-// (modes 0..n/2-1; the n/2 mode is dropped).  in and out may alias.
-hipError_t launch_zfwd(int n, const float* in, float2* out, long nrows, const float2* tw,
+// Forward real-to-complex z pass of nfields fields: rows of n reals (in.p[f] as float
+// rows) -> rows of n/2 complex (modes 0..n/2-1; the n/2 mode is dropped).  in and out may
+// alias.
+hipError_t launch_zfwd(int n, FieldPtrs in, FieldPtrs out, int nfields, long nrows, const float2* tw,
                        hipStream_t st);
 // Inverse complex-to-real z pass for nfields fields; field f reads in.p[f], writes
 // out.p[f] (as float rows).  May alias.
@@ -81,10 +82,11 @@ hipError_t launch_shell_stats(int n, const float2* a, const float2* b, double* p
 // Inverse column pass of one field with two outputs: out_d = inverse transform of
 // i n X (n the signed mode number along the column) and out_p = inverse transform of
 // X.  The three buffers are distinct.  in is rotated by rot as the input of an
-// inverse y pass of launch_col; the outputs are plain.
+// inverse y pass of launch_col; the outputs are plain.  x_io (optional, n < 768, distinct
+// from the others): a field whose inverse pass runs in place in the same launch.
 hipError_t launch_col_pair(int n, const float2* in, float2* out_p, float2* out_d, int n_outer, long outer_stride,
                            long inner_stride, int ncols, const float2* tw, int width, int rot, hipStream_t st,
-                           int reverse = 0);
+                           int reverse = 0, float2* x_io = nullptr);
 // x pass with the k-space multiplier: forward x transform of `in`, multiply, inverse
 // x transform into each of nout outputs.  Layout [x][y][kz] with n/2 kz per row, the
 // rows of every x plane rotated by rot (input and outputs alike), rot a multiple of

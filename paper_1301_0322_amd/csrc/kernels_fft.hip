@@ -107,15 +107,16 @@ __device__ __forceinline__ const float2* z_twiddles(float2* stw, const float2* _
 // where Z is the length-M = N/2 DFT of z[m] = x[2m] + i x[2m+1].  Z[M-k] sits in the
 // partner lane of the same wave (Pencil::partner).
 // ---------------------------------------------------------------------------------
+// blockIdx.y selects the field.
 template <int N>
-__global__ __launch_bounds__(ZPencil<N>::T) void k_zfwd(const float* in, float2* out, const float2* __restrict__ tw) {
+__global__ __launch_bounds__(ZPencil<N>::T) void k_zfwd(FieldPtrs in, FieldPtrs out, const float2* __restrict__ tw) {
   using P = ZPencil<N>;
   constexpr int M = N / 2;
   __shared__ __align__(16) float2 ex[P::LDS];
   __shared__ float2 stw_l[z_stw_len<N>()];
   const long row0 = (long)blockIdx.x * P::NT;
   float2 a[P::R2];
-  P::load_a(a, reinterpret_cast<const float2*>(in) + row0 * M, M);
+  P::load_a(a, in.p[blockIdx.y] + row0 * M, M);
   const float2* stw = z_twiddles<N>(stw_l, tw);
   __syncthreads();
   float2 q[P::UB][P::R1];
@@ -136,7 +137,7 @@ __global__ __launch_bounds__(ZPencil<N>::T) void k_zfwd(const float* in, float2*
       q[u][j1] = c_add(s, mul_si<-1>(c_mul(stw[k], d)));
     }
   }
-  P::store_b(q, out + row0 * M, M);
+  P::store_b(q, out.p[blockIdx.y] + row0 * M, M);
 }
 
 // ---------------------------------------------------------------------------------
@@ -297,14 +298,17 @@ __global__ __launch_bounds__((Pencil<N, B, false>::T)) void k_col(FieldPtrs in, 
 // in registers and writes both outputs (the LDS already limits the pass to two waves
 // per SIMD, which leave room for the second copy).  in may be a rotated half spectrum
 // (rot, plane index o); the outputs are not rotated.
+// With x_io (two-block form only) a third block per tile runs the plain inverse pass of
+// that field in place: one launch for the three y passes of a force.
 template <int N>
 constexpr bool col_pair_one_block() { return N >= 768; }
 
 template <int N, int B>
 __global__ __launch_bounds__((Pencil<N, B, false>::T)) void k_col_pair(const float2* __restrict__ in,
                                                                      float2* __restrict__ out_p,
-                                                                     float2* __restrict__ out_d, long outer_stride,
-                                                                     long inner_stride, int ntiles_c, long ntiles,
+                                                                     float2* __restrict__ out_d, float2* x_io,
+                                                                     long outer_stride, long inner_stride,
+                                                                     int ntiles_c, long ntiles,
                                                                      const float2* __restrict__ tw, int reverse,
                                                                      int rot) {
   using P = Pencil<N, B, false>;
@@ -312,24 +316,27 @@ __global__ __launch_bounds__((Pencil<N, B, false>::T)) void k_col_pair(const flo
   __shared__ float2 stw[N];
   constexpr bool ONE = col_pair_one_block<N>();
   long tile;
-  int deriv;
+  int role = 0;   // 0: i n X of in, 1: X of in, 2: X of x_io
   if (ONE) {
     tile = blockIdx.x;
-    deriv = 1;
-  } else if (ntiles % kXcdsFft == 0) {
-    const long g = blockIdx.x / (2 * kXcdsFft), w = blockIdx.x % (2 * kXcdsFft);
-    tile = g * kXcdsFft + w % kXcdsFft;
-    deriv = w < kXcdsFft;
   } else {
-    tile = blockIdx.x / 2;
-    deriv = (blockIdx.x % 2) == 0;
+    const int roles = x_io ? 3 : 2;
+    if (ntiles % kXcdsFft == 0) {
+      const long g = blockIdx.x / (roles * kXcdsFft), w = blockIdx.x % (roles * kXcdsFft);
+      tile = g * kXcdsFft + w % kXcdsFft;
+      role = (int)(w / kXcdsFft);
+    } else {
+      tile = blockIdx.x / roles;
+      role = (int)(blockIdx.x % roles);
+    }
   }
   if (reverse) tile = ntiles - 1 - tile;
   const int tc = (int)(tile % ntiles_c);
   const long o = tile / ntiles_c;
   const long origin = o * outer_stride + (long)tc * B;
   float2 a[P::R2];
-  P::load_a_rows(a, in + origin, [&](int m) { return (long)rot_row<N>(m, (int)o, rot) * inner_stride; });
+  P::load_a_rows(a, (role == 2 ? x_io : in) + origin,
+                 [&](int m) { return (long)rot_row<N>(m, (int)o, rot) * inner_stride; });
   load_twiddles(stw, tw, N);
   // i n X of A-layout register i2 (position m = i1 + R1 i2)
   auto times_in = [&](int i2, float2 v) {
@@ -350,13 +357,13 @@ __global__ __launch_bounds__((Pencil<N, B, false>::T)) void k_col_pair(const flo
     P::template fwd_like<1, 1>(a, q, ex, stw);
     P::store_b(q, out_p + origin, inner_stride);
   } else {
-    if (deriv) {
+    if (role == 0) {
 #pragma unroll
       for (int i2 = 0; i2 < P::R2; ++i2) a[i2] = times_in(i2, a[i2]);
     }
     __syncthreads();
     P::template fwd_like<1, 1>(a, q, ex, stw);
-    P::store_b(q, (deriv ? out_d : out_p) + origin, inner_stride);
+    P::store_b(q, (role == 0 ? out_d : role == 1 ? out_p : x_io) + origin, inner_stride);
   }
 }
 
@@ -555,10 +562,10 @@ bool fft_size_supported(int n) {
 }
 
 template <int N>
-static hipError_t zfwd_t(const float* in, float2* out, long nrows, const float2* tw, hipStream_t st) {
+static hipError_t zfwd_t(FieldPtrs in, FieldPtrs out, int nf, long nrows, const float2* tw, hipStream_t st) {
   using P = ZPencil<N>;
-  if (nrows % P::NT) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_zfwd<N>, dim3(nrows / P::NT), dim3(P::T), 0, st, in, out, tw);
+  if (nrows % P::NT || nf < 1 || nf > kMaxFields) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_zfwd<N>, dim3((unsigned)(nrows / P::NT), nf), dim3(P::T), 0, st, in, out, tw);
   return hipGetLastError();
 }
 
@@ -619,15 +626,16 @@ static hipError_t col_t(int dir, FieldPtrs in, FieldPtrs out, int nf, int n_oute
 }
 
 template <int N, int B>
-static hipError_t col_pair_tb(const float2* in, float2* out_p, float2* out_d, int n_outer, long outer_stride,
+static hipError_t col_pair_tb(const float2* in, float2* out_p, float2* out_d, float2* x_io, int n_outer, long outer_stride,
                               long inner_stride, int ncols, const float2* tw, int reverse, int rot, hipStream_t st) {
   if constexpr (col_ok<N, B>()) {
     if (ncols % B) return hipErrorInvalidValue;
     constexpr int T = Pencil<N, B, false>::T;
     const int ntc = ncols / B;
     const long ntiles = (long)n_outer * ntc;
-    const long nblocks = col_pair_one_block<N>() ? ntiles : 2 * ntiles;
-    hipLaunchKernelGGL((k_col_pair<N, B>), dim3((unsigned)nblocks), dim3(T), 0, st, in, out_p, out_d,
+    if (x_io && col_pair_one_block<N>()) return hipErrorInvalidValue;
+    const long nblocks = col_pair_one_block<N>() ? ntiles : (x_io ? 3 : 2) * ntiles;
+    hipLaunchKernelGGL((k_col_pair<N, B>), dim3((unsigned)nblocks), dim3(T), 0, st, in, out_p, out_d, x_io,
                        outer_stride, inner_stride, ntc, ntiles, tw, reverse, rot);
     return hipGetLastError();
   } else {
@@ -636,16 +644,16 @@ static hipError_t col_pair_tb(const float2* in, float2* out_p, float2* out_d, in
 }
 
 template <int N>
-static hipError_t col_pair_t(const float2* in, float2* out_p, float2* out_d, int n_outer, long outer_stride,
+static hipError_t col_pair_t(const float2* in, float2* out_p, float2* out_d, float2* x_io, int n_outer, long outer_stride,
                              long inner_stride, int ncols, const float2* tw, int width, int reverse, int rot,
                              hipStream_t st) {
   switch (width ? width : col_width_default<N>()) {
     case 4:
-      return col_pair_tb<N, 4>(in, out_p, out_d, n_outer, outer_stride, inner_stride, ncols, tw, reverse, rot, st);
+      return col_pair_tb<N, 4>(in, out_p, out_d, x_io, n_outer, outer_stride, inner_stride, ncols, tw, reverse, rot, st);
     case 8:
-      return col_pair_tb<N, 8>(in, out_p, out_d, n_outer, outer_stride, inner_stride, ncols, tw, reverse, rot, st);
+      return col_pair_tb<N, 8>(in, out_p, out_d, x_io, n_outer, outer_stride, inner_stride, ncols, tw, reverse, rot, st);
     case 16:
-      return col_pair_tb<N, 16>(in, out_p, out_d, n_outer, outer_stride, inner_stride, ncols, tw, reverse, rot, st);
+      return col_pair_tb<N, 16>(in, out_p, out_d, x_io, n_outer, outer_stride, inner_stride, ncols, tw, reverse, rot, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -735,11 +743,11 @@ int fft_rot_rows(int n) { return fft_size_supported(n) ? pencil_r2(n) : 0; }
 // pass's access pattern move 2.7 TB/s over plain planes and 3.7 TB/s over rotated ones.
 bool fft_rot_default_on(int n) { return n >= 1024; }
 
-hipError_t launch_zfwd(int n, const float* in, float2* out, long nrows, const float2* tw, hipStream_t st) {
+hipError_t launch_zfwd(int n, FieldPtrs in, FieldPtrs out, int nf, long nrows, const float2* tw, hipStream_t st) {
   switch (n) {
 #define COLA_CASE(N) \
   case N:            \
-    return zfwd_t<N>(in, out, nrows, tw, st);
+    return zfwd_t<N>(in, out, nf, nrows, tw, st);
     COLA_FOR_EACH_SIZE(COLA_CASE)
 #undef COLA_CASE
     default:
@@ -887,13 +895,14 @@ hipError_t launch_shell_stats(int n, const float2* a, const float2* b, double* p
 
 hipError_t launch_col_pair(int n, const float2* in, float2* out_p, float2* out_d, int n_outer, long outer_stride,
                            long inner_stride, int ncols, const float2* tw, int width, int rot, hipStream_t st,
-                           int reverse) {
+                           int reverse, float2* x_io) {
   if (out_d == in || out_p == in || out_d == out_p) return hipErrorInvalidValue;
+  if (x_io && (x_io == in || x_io == out_p || x_io == out_d)) return hipErrorInvalidValue;
   if (rot < 0 || rot >= n) return hipErrorInvalidValue;
   switch (n) {
 #define COLA_CASE(N) \
   case N:            \
-    return col_pair_t<N>(in, out_p, out_d, n_outer, outer_stride, inner_stride, ncols, tw, width, reverse, rot, st);
+    return col_pair_t<N>(in, out_p, out_d, x_io, n_outer, outer_stride, inner_stride, ncols, tw, width, reverse, rot, st);
     COLA_FOR_EACH_SIZE(COLA_CASE)
 #undef COLA_CASE
     default:
