@@ -910,7 +910,8 @@ int cola_density(cola_plan p, const float* s, float* rho, void* ws, void* stream
   return deposit_into(p, s, rho, static_cast<float*>(ws), (hipStream_t)stream);
 }
 
-// Forward 3D transform of the real field in ws mesh m (in place, half spectrum).
+// Forward 3D transform of the real field in ws mesh m (in place, half spectrum; modes
+// outside the sphere of complete shells are left unfinished).
 int fft_forward(cola_plan p, float* g, hipStream_t st) {
   const int n = p->cfg.nm;
   const long h = n / 2;
@@ -920,7 +921,7 @@ int fft_forward(cola_plan p, float* g, hipStream_t st) {
   COLA_TRY(ypass(p, kStYFwd, n, -1, fields({g}), 1, tw, st, 0));
   // x: columns along x (stride n h) in tiles of kz at fixed y
   return hip_status(traced(p, kStAnalysis, st, [&] {
-    return launch_col(n, -1, fields({g}), fields({g}), 1, n, h, (long)n * h, (int)h, tw, p->fft_width[1], 0, st);
+    return launch_col(n, -1, fields({g}), fields({g}), 1, n, h, (long)n * h, (int)h, tw, p->fft_width[1], 0, st, 0, 1);
   }));
 }
 

@@ -70,9 +70,10 @@ hipError_t launch_zinv_hessian(int n, FieldPtrs in, float* out, long nrows, cons
 // side (output of dir < 0, input of dir > 0) is a rotated half spectrum: row y of plane
 // x at row (y + rot x) mod n.  0 for the plain layout and for passes along x.
 // reverse: blocks take the tiles from the last to the first.
+// ball: skip tiles outside the sphere of complete shells (forward x passes, outer = y).
 hipError_t launch_col(int n, int dir, FieldPtrs in, FieldPtrs out, int nfields, int n_outer,
                       long outer_stride, long inner_stride, int ncols, const float2* tw, int width, int rot,
-                      hipStream_t st, int reverse = 0);
+                      hipStream_t st, int reverse = 0, int ball = 0);
 // Shell statistics of one or two half spectra (b may be null) into out[6][n/2]
 // (doubles, row r, shell s = round(|n|) for 1 <= s < n/2; s = 0 stays zero): mode
 // count, P_aa, P_bb, P_ab (sums / count * norm), rho and n_max.  part holds

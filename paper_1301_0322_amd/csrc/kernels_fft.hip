@@ -265,11 +265,14 @@ __global__ __launch_bounds__(ZHPencil<N>::T) void k_zinv_hess(FieldPtrs in, floa
 // (still in the memory-side cache).
 // rot: the k-space side (the output of a forward pass, the input of an inverse one) is
 // a rotated half spectrum whose plane index is the outer index o (y passes only).
+// ball (x passes of the shell statistics, outer index y): tiles whose modes all lie
+// outside the sphere of complete shells (n_y^2 + k_z^2 > h^2 - h, h = n/2: shell h or
+// more) are left as they are, about a fifth of them; nothing reads those modes.
 template <int N, int B, int S>
 __global__ __launch_bounds__((Pencil<N, B, false>::T)) void k_col(FieldPtrs in, FieldPtrs out, long outer_stride,
                                                                 long inner_stride, int ntiles_c,
                                                                 const float2* __restrict__ tw, int reverse,
-                                                                int rot) {
+                                                                int rot, int ball) {
   using P = Pencil<N, B, false>;
   __shared__ __align__(16) float2 ex[P::LDS];
   __shared__ float2 stw[N];
@@ -277,6 +280,10 @@ __global__ __launch_bounds__((Pencil<N, B, false>::T)) void k_col(FieldPtrs in, 
   const unsigned blk = reverse ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
   const int tc = blk % ntiles_c;
   const long o = blk / ntiles_c;
+  if (ball) {
+    const int ny = min((int)o, N - (int)o), kz = tc * B;
+    if (ny * ny + kz * kz > (N / 2) * (N / 2) - N / 2) return;
+  }
   const long origin = o * outer_stride + (long)tc * B;
   const int rot_in = S > 0 ? rot : 0, rot_out = S < 0 ? rot : 0;
   float2 a[P::R2];
@@ -595,7 +602,8 @@ static hipError_t zinv_hess_t(FieldPtrs in, float* out, long nrows, const float2
 
 template <int N, int B>
 static hipError_t col_tb(int dir, FieldPtrs in, FieldPtrs out, int nf, int n_outer, long outer_stride,
-                         long inner_stride, int ncols, const float2* tw, int reverse, int rot, hipStream_t st) {
+                         long inner_stride, int ncols, const float2* tw, int reverse, int rot, int ball,
+                         hipStream_t st) {
   if constexpr (col_ok<N, B>()) {
     if (ncols % B) return hipErrorInvalidValue;
     constexpr int T = Pencil<N, B, false>::T;
@@ -603,10 +611,10 @@ static hipError_t col_tb(int dir, FieldPtrs in, FieldPtrs out, int nf, int n_out
     dim3 grid((unsigned)((long)n_outer * ntc), nf);
     if (dir < 0)
       hipLaunchKernelGGL((k_col<N, B, -1>), grid, dim3(T), 0, st, in, out, outer_stride, inner_stride, ntc, tw,
-                         reverse, rot);
+                         reverse, rot, ball);
     else
       hipLaunchKernelGGL((k_col<N, B, 1>), grid, dim3(T), 0, st, in, out, outer_stride, inner_stride, ntc, tw,
-                         reverse, rot);
+                         reverse, rot, ball);
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;
@@ -616,11 +624,11 @@ static hipError_t col_tb(int dir, FieldPtrs in, FieldPtrs out, int nf, int n_out
 template <int N>
 static hipError_t col_t(int dir, FieldPtrs in, FieldPtrs out, int nf, int n_outer, long outer_stride,
                         long inner_stride, int ncols, const float2* tw, int width, int reverse, int rot,
-                        hipStream_t st) {
+                        int ball, hipStream_t st) {
   switch (width ? width : col_width_default<N>()) {
-    case 4: return col_tb<N, 4>(dir, in, out, nf, n_outer, outer_stride, inner_stride, ncols, tw, reverse, rot, st);
-    case 8: return col_tb<N, 8>(dir, in, out, nf, n_outer, outer_stride, inner_stride, ncols, tw, reverse, rot, st);
-    case 16: return col_tb<N, 16>(dir, in, out, nf, n_outer, outer_stride, inner_stride, ncols, tw, reverse, rot, st);
+    case 4: return col_tb<N, 4>(dir, in, out, nf, n_outer, outer_stride, inner_stride, ncols, tw, reverse, rot, ball, st);
+    case 8: return col_tb<N, 8>(dir, in, out, nf, n_outer, outer_stride, inner_stride, ncols, tw, reverse, rot, ball, st);
+    case 16: return col_tb<N, 16>(dir, in, out, nf, n_outer, outer_stride, inner_stride, ncols, tw, reverse, rot, ball, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -783,12 +791,12 @@ hipError_t launch_zinv_hessian(int n, FieldPtrs in, float* out, long nrows, cons
 
 hipError_t launch_col(int n, int dir, FieldPtrs in, FieldPtrs out, int nf, int n_outer, long outer_stride,
                       long inner_stride, int ncols, const float2* tw, int width, int rot, hipStream_t st,
-                      int reverse) {
+                      int reverse, int ball) {
   if (rot < 0 || rot >= n) return hipErrorInvalidValue;
   switch (n) {
 #define COLA_CASE(N) \
   case N:            \
-    return col_t<N>(dir, in, out, nf, n_outer, outer_stride, inner_stride, ncols, tw, width, reverse, rot, st);
+    return col_t<N>(dir, in, out, nf, n_outer, outer_stride, inner_stride, ncols, tw, width, reverse, rot, ball, st);
     COLA_FOR_EACH_SIZE(COLA_CASE)
 #undef COLA_CASE
     default:
@@ -801,10 +809,15 @@ hipError_t launch_col(int n, int dir, FieldPtrs in, FieldPtrs out, int nf, int n
 // plane is not stored, so shells s = round(|n|) with 1 <= s < n/2 are complete).
 // Per shell: the mode count and the sums of |a|^2, |b|^2 and Re(a conj b), each mode
 // with kz > 0 counted twice (it stands for its conjugate partner too).  The shell is
-// decided in integers.  Blocks accumulate in LDS (FP64 atomics) over a contiguous
-// range of elements and write partial sums; k_shell_reduce adds the partials block
-// by block in a fixed order and forms P, rho = P_ab / sqrt(P_aa P_bb) and
-// n_max = (2/3) rho / sqrt(1 - rho^2).
+// decided in integers.
+// The eight modes (+-nx, +-ny, kz), (+-ny, +-nx, kz) share a shell: a thread adds up its
+// eight (four on an axis or the diagonal, one at the origin) in FP64 registers and puts
+// one set of sums into the block's shells in LDS.  FP64 LDS atomics on few addresses cost
+// about a cycle a lane, which bounded the kernel when every mode had its own (512^3, two
+// fields: 0.400 -> 0.158 ms).  Blocks write partial sums; k_shell_reduce adds the
+// partials in a fixed order, 16 slices of the blocks per shell side by side (one thread
+// per shell walked all 1024 of them alone: 0.294 -> 0.024 ms), and forms P,
+// rho = P_ab / sqrt(P_aa P_bb) and n_max = (2/3) rho / sqrt(1 - rho^2).
 // ---------------------------------------------------------------------------------
 constexpr int kShellThreads = 256;
 
@@ -815,49 +828,83 @@ __device__ __forceinline__ int shell_of(int n2) {
   return n2 > s * s + s ? s + 1 : s;   // round(sqrt(n2)): sqrt(n2) >= s + 1/2 iff n2 > s^2 + s
 }
 
+// Pair p of 0 <= x <= y: p = y (y + 1) / 2 + x.
+__device__ __forceinline__ void triangle(long p, int& x, int& y) {
+  y = (int)((sqrtf(8.f * (float)p + 1.f) - 1.f) * 0.5f);
+  while ((long)y * (y + 1) / 2 > p) --y;
+  while ((long)(y + 1) * (y + 2) / 2 <= p) ++y;
+  x = (int)(p - (long)y * (y + 1) / 2);
+}
+
 __global__ __launch_bounds__(kShellThreads) void k_shell_sums(int n, const float2* __restrict__ a,
-                                                              const float2* __restrict__ b, long chunk,
+                                                              const float2* __restrict__ b, long total,
                                                               double* __restrict__ part) {
   extern __shared__ double acc[];   // [4][h]: count, aa, bb, ab
   const int h = n / 2;
   for (int i = threadIdx.x; i < 4 * h; i += kShellThreads) acc[i] = 0.0;
   __syncthreads();
-  const long total = (long)n * n * h;
-  const long beg = (long)blockIdx.x * chunk;
-  const long end = beg + chunk < total ? beg + chunk : total;
-  for (long e = beg + threadIdx.x; e < end; e += kShellThreads) {
+  for (long e = (long)blockIdx.x * kShellThreads + threadIdx.x; e < total; e += (long)gridDim.x * kShellThreads) {
     const int kz = (int)(e % h);
-    const long r = e / h;
-    const int y = (int)(r % n), x = (int)(r / n);
-    const int nx = x <= h ? x : x - n, ny = y <= h ? y : y - n;
-    const int sh = shell_of(nx * nx + ny * ny + kz * kz);
+    int x, y;
+    triangle(e / h, x, y);   // x, y < h: a Nyquist index is past the complete shells
+    const int sh = shell_of(x * x + y * y + kz * kz);
     if (sh < 1 || sh >= h) continue;
+    // r bit 0: -x, bit 1: -y, bit 2: exchanged.  A row that repeats another (x or y is 0,
+    // or x = y) is loaded with weight 0, so that no load waits behind a branch.
+    float2 va[8], vb[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const int rx = (r & 1) && x ? n - x : x, ry = (r & 2) && y ? n - y : y;
+      const long i = (r & 4 ? (long)ry * n + rx : (long)rx * n + ry) * h + kz;
+      va[r] = a[i];
+      if (b) vb[r] = b[i];
+    }
+    double aa = 0.0, bb = 0.0, ab = 0.0;
+    int rows = 0;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const bool once = !((r & 1) && x == 0) && !((r & 2) && y == 0) && !((r & 4) && x == y);
+      const double u = once ? 1.0 : 0.0;
+      aa += u * ((double)va[r].x * va[r].x + (double)va[r].y * va[r].y);
+      if (b) {
+        bb += u * ((double)vb[r].x * vb[r].x + (double)vb[r].y * vb[r].y);
+        ab += u * ((double)va[r].x * vb[r].x + (double)va[r].y * vb[r].y);
+      }
+      rows += once;
+    }
     const double w = kz > 0 ? 2.0 : 1.0;
-    const float2 va = a[e];
-    atomicAdd(&acc[sh], w);
-    atomicAdd(&acc[h + sh], w * ((double)va.x * va.x + (double)va.y * va.y));
+    atomicAdd(&acc[sh], w * rows);
+    atomicAdd(&acc[h + sh], w * aa);
     if (b) {
-      const float2 vb = b[e];
-      atomicAdd(&acc[2 * h + sh], w * ((double)vb.x * vb.x + (double)vb.y * vb.y));
-      atomicAdd(&acc[3 * h + sh], w * ((double)va.x * vb.x + (double)va.y * vb.y));
+      atomicAdd(&acc[2 * h + sh], w * bb);
+      atomicAdd(&acc[3 * h + sh], w * ab);
     }
   }
   __syncthreads();
   for (int i = threadIdx.x; i < 4 * h; i += kShellThreads) part[(long)blockIdx.x * 4 * h + i] = acc[i];
 }
 
+constexpr int kReduceShells = 16;   // shells per block, each by kShellThreads / 16 threads
+
 __global__ __launch_bounds__(kShellThreads) void k_shell_reduce(int h, const double* __restrict__ part, int nblocks,
                                                                 double norm, int cross, double* __restrict__ out) {
-  const int sh = blockIdx.x * kShellThreads + threadIdx.x;
-  if (sh >= h) return;
-  double c = 0.0, aa = 0.0, bb = 0.0, ab = 0.0;
-  for (int k = 0; k < nblocks; ++k) {
-    const double* q = part + (long)k * 4 * h;
-    c += q[sh];
-    aa += q[h + sh];
-    bb += q[2 * h + sh];
-    ab += q[3 * h + sh];
-  }
+  constexpr int kSlices = kShellThreads / kReduceShells;
+  __shared__ double sums[4][kSlices][kReduceShells];
+  const int ls = threadIdx.x % kReduceShells, slice = threadIdx.x / kReduceShells;
+  const int sh = blockIdx.x * kReduceShells + ls;
+  double v[4] = {0.0, 0.0, 0.0, 0.0};
+  if (sh < h)
+    for (int k = slice; k < nblocks; k += kSlices)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] += part[((long)k * 4 + q) * h + sh];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) sums[q][slice][ls] = v[q];
+  __syncthreads();
+  if (slice != 0 || sh >= h) return;
+  for (int k = 1; k < kSlices; ++k)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] += sums[q][k][ls];
+  const double c = v[0], aa = v[1], bb = v[2], ab = v[3];
   double paa = 0.0, pbb = 0.0, pab = 0.0, rho = 0.0, nmax = 0.0;
   if (c > 0.0) {
     paa = aa / c * norm;
@@ -880,15 +927,13 @@ hipError_t launch_shell_stats(int n, const float2* a, const float2* b, double* p
                               double* out, hipStream_t st) {
   if (n < 4 || n % 2 || !a || !part || !out) return hipErrorInvalidValue;
   const int h = n / 2;
-  const long total = (long)n * n * h;
+  const long total = (long)h * (h + 1) / 2 * h;   // (x <= y, kz) with all indices below h
   long nb = part_doubles / (4L * h);
-  nb = nb < 1024 ? nb : 1024;
+  nb = min(nb, min(1024L, (total + kShellThreads - 1) / kShellThreads));
   if (nb < 1) return hipErrorInvalidValue;
-  const long chunk = (total + nb - 1) / nb;
-  nb = (total + chunk - 1) / chunk;
-  hipLaunchKernelGGL(k_shell_sums, dim3((unsigned)nb), dim3(kShellThreads), 4 * h * sizeof(double), st, n, a, b, chunk,
+  hipLaunchKernelGGL(k_shell_sums, dim3((unsigned)nb), dim3(kShellThreads), 4 * h * sizeof(double), st, n, a, b, total,
                      part);
-  hipLaunchKernelGGL(k_shell_reduce, dim3((unsigned)((h + kShellThreads - 1) / kShellThreads)), dim3(kShellThreads), 0,
+  hipLaunchKernelGGL(k_shell_reduce, dim3((unsigned)((h + kReduceShells - 1) / kReduceShells)), dim3(kShellThreads), 0,
                      st, h, part, (int)nb, norm, b != nullptr ? 1 : 0, out);
   return hipGetLastError();
 }
