@@ -558,7 +558,7 @@ struct AdjLayout {
   float* lam_s1;
   float* lam_s2;
   float* lpt;       // 10 np^3
-  unsigned* wmax;   // four words: max |weight| of the weighted deposit
+  unsigned* wmax;   // four words, two used in turn: max |weight| of a step's weighted deposit
   size_t bytes;
 };
 
@@ -617,8 +617,9 @@ int run_adjoint(cola_plan p, const float* w, const float* ckpt, const float* dL_
   const float mass = (float)std::pow((double)lat.ratio, 3);
   const bool plain = p->cfg.flags & COLA_FLAG_NO_LPT_FRAME;
   const int nm = p->cfg.nm;
-  for (float* x : {L.lam_s, L.lam_v, L.lam_s1, L.lam_s2})
-    COLA_HIP(traced(p, kStAdjKick, st, [&] { return launch_fill(x, n3, 0.0f, st); }));
+  // lam_s, lam_v, lam_s1, lam_s2 lie together
+  COLA_HIP(traced(p, kStAdjKick, st, [&] { return launch_fill(L.lam_s, 4 * n3, 0.0f, st); }));
+  COLA_HIP(traced(p, kStAdjKick, st, [&] { return launch_fill(reinterpret_cast<float*>(L.wmax), 4, 0.0f, st); }));
   // dL/ds at the end: derivative of the CIC density of s_n against dL/drho.
   const float* s_end = ckpt + (long)ns * n3;
   COLA_TRY(bin_only(p, s_end, ws, st));
@@ -641,15 +642,17 @@ int run_adjoint(cola_plan p, const float* w, const float* ckpt, const float* dL_
     a.t2d2 = plain ? 0.0f : (float)row.g.t2d2;
     a.dd1 = plain ? 0.0f : (float)row.dd1;
     a.dd2 = plain ? 0.0f : (float)row.dd2;
-    COLA_HIP(traced(p, kStAdjKick, st,
-                    [&] { return launch_adj_kick_drift(n3, a, L.lam_s, L.lam_v, L.lam_s1, L.lam_s2, st); }));
+    unsigned* wmax = L.wmax + (i & 1);   // the other word is cleared for the next step
+    COLA_HIP(traced(p, kStAdjKick, st, [&] {
+      return launch_adj_kick_drift(n3, a, L.lam_s, L.lam_v, L.lam_s1, L.lam_s2, wmax, L.wmax + ((i & 1) ^ 1), st);
+    }));
     // recompute the force mesh at s_i (bins for s_i stay valid)
     COLA_TRY(pm_mesh(p, s_i, row.a, ws, st));
     // nu_d = mass-weighted CIC deposit of mu_d = lam_v_d
     const BinBuffers bb = bin_buffers(p, ws);
     // the three components in one particle walk (amesh[d] = amesh[0] + d nm^3)
     COLA_HIP(traced(p, kStAdjDeposit, st, [&] {
-      return launch_deposit3(lat, b, s_i, bb, L.amesh[0], mass, L.lam_v, L.wmax, st);
+      return launch_deposit3(lat, b, s_i, bb, L.amesh[0], mass, L.lam_v, wmax, st);
     }));
     // rbar = sum_d K_d^T nu_d (conjugate multiplier), into amesh[0]
     const float2* tw = p->d_tw_nm;

@@ -175,10 +175,10 @@ hipError_t launch_deposit(Lattice lat, Bins b, const float* s, BinBuffers bb, fl
                           hipStream_t st, const int* lag = nullptr);
 // Three weighted deposits in one particle walk: rho + c nm^3 receives the CIC deposit
 // of mass * weight[c n + Lagrangian index], c = 0..2 (s SoA in Lagrangian order), summed
-// in 64-bit fixed point after scaling by a power of two from max |weight| (computed into
-// wmax, four words of device scratch).  Deterministic: independent of particle order.
+// in 64-bit fixed point after scaling by a power of two from max |weight|, whose bits are
+// in *wmax (launch_adj_kick_drift).  Deterministic: independent of particle order.
 hipError_t launch_deposit3(Lattice lat, Bins b, const float* s, BinBuffers bb, float* rho, float mass,
-                           const float* weight, unsigned* wmax, hipStream_t st);
+                           const float* weight, const unsigned* wmax, hipStream_t st);
 
 struct KickArgs {
   float alpha;                 // kick factor
@@ -262,8 +262,9 @@ hipError_t launch_grad_gather(Lattice lat, Bins b, BinBuffers bb, const float* s
 struct AdjStepArgs {
   float alpha, beta, t2d1, t2d2, dd1, dd2;
 };
+// n3 is a multiple of 4.  max |new lam_v| goes to *wmax (zero on entry); *wmax_next (another word) is cleared.
 hipError_t launch_adj_kick_drift(long n3, AdjStepArgs a, float* lam_s, float* lam_v, float* lam_s1, float* lam_s2,
-                                 hipStream_t st);
+                                 unsigned* wmax, unsigned* wmax_next, hipStream_t st);
 hipError_t launch_axpy(long n, float a, const float* x, float* y, hipStream_t st);
 struct HessPtrs {
   float* p[6];

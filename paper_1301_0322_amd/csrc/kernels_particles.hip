@@ -614,8 +614,14 @@ constexpr unsigned long long kRangeMask = 0x7566344210ull, kRangeBeg = 0x5552451
 
 // NW weight planes (weighted deposits): NW = 1 deposits mass * weight[lag]; NW = 3
 // deposits the three planes weight[c n + lag] into rho + c nm^3 in one particle walk.
+// Threads of a deposit block.  The three accumulator planes of a weighted deposit take 48 KB
+// at depth 32, three blocks to a CU: 512 threads a block keep 24 waves there instead of 12
+// (128^3 particles, 256^3 cells: 0.167 -> 0.142 ms).
+template <int TZ, int NW>
+constexpr int deposit_threads() { return NW == 3 && TileDims<TZ>::TT < 512 && TZ >= 32 ? 2 * TileDims<TZ>::TT : TileDims<TZ>::TT; }
+
 template <int TZ, class ACC, int NW = 1>
-__global__ __launch_bounds__(TileDims<TZ>::TT) void k_deposit_tiles(Lattice lat, Bins bins, const float* __restrict__ s,
+__global__ __launch_bounds__((deposit_threads<TZ, NW>())) void k_deposit_tiles(Lattice lat, Bins bins, const float* __restrict__ s,
                                                                 const int* __restrict__ lag,
                                                                 const int* __restrict__ idx,
                                                                 const int* __restrict__ offset,
@@ -623,6 +629,7 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_deposit_tiles(Lattice lat,
                                                                 float mass, const float* __restrict__ weight,
                                                                 const unsigned* __restrict__ wmax) {
   using D = TileDims<TZ>;
+  constexpr int T = deposit_threads<TZ, NW>();
   static_assert(NW == 1 || NW == 3, "one or three weight planes");
   __shared__ ACC tile[NW * D::CORE];
   // Weighted fixed-point deposits (wmax = bits of max |weight|): the weights are scaled
@@ -648,7 +655,7 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_deposit_tiles(Lattice lat,
   TileGeom g;
   bool listed;
   if (!tile_geom<TZ>(bins, heavy, g, listed)) return;
-  for (int i = threadIdx.x; i < NW * D::CORE; i += D::TT) tile[i] = 0;
+  for (int i = threadIdx.x; i < NW * D::CORE; i += T) tile[i] = 0;
   if (threadIdx.x < 64) {
     // lane r < kDepRanges describes range r
     const int lane = threadIdx.x;
@@ -686,14 +693,14 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_deposit_tiles(Lattice lat,
   // flight per batch on that block's long serial loop.
   auto walk = [&](auto slots) {
   constexpr int U = decltype(slots)::value;
-  for (int base = 0; base < total; base += U * D::TT) {   // block-uniform trip count
+  for (int base = 0; base < total; base += U * T) {   // block-uniform trip count
     float sv[U][3];
     unsigned lg[U];
     int msk[U];
     bool in[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int i = base + u * D::TT + (int)threadIdx.x;
+      const int i = base + u * T + (int)threadIdx.x;
       in[u] = i < total;
       const int ii = in[u] ? i : 0;
       int r = 0;
@@ -756,12 +763,12 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_deposit_tiles(Lattice lat,
   // A thread's runs are 4 TT cells apart, a whole number of x planes of the tile, so its
   // output address advances by a fixed stride.
   static_assert(TZ % 4 == 0, "16-byte row pieces");
-  static_assert((4 * D::TT) % (TZ * kTY) == 0, "runs a whole number of x planes apart");
+  static_assert((4 * T) % (TZ * kTY) == 0, "runs a whole number of x planes apart");
   const long nm = lat.nm;
   const int i0 = 4 * threadIdx.x;
   float* out = rho + ((g.lo[0] + i0 / (TZ * kTY)) * nm + g.lo[1] + (i0 / TZ) % kTY) * nm + g.lo[2] + i0 % TZ;
-  const long stride = (long)(4 * D::TT / (TZ * kTY)) * nm * nm;
-  for (int i = i0; i < D::CORE; i += 4 * D::TT, out += stride) {
+  const long stride = (long)(4 * T / (TZ * kTY)) * nm * nm;
+  for (int i = i0; i < D::CORE; i += 4 * T, out += stride) {
 #pragma unroll
     for (int c = 0; c < NW; ++c) {
       const ACC* v = tile + c * D::CORE + i;
@@ -1220,43 +1227,11 @@ hipError_t launch_bin_scatter(Lattice lat, BinBuffers bb, hipStream_t st) {
   return hipGetLastError();
 }
 
-// max |x| over count floats into *out (which the caller clears), as the bits of a
-// non-negative float, whose unsigned order is the numeric order with +inf above every
-// finite value and NaN above +inf: a non-finite entry gives a non-finite maximum.
-// One atomic per block: atomics on a single address serialise in L2, so the waves of a
-// block combine their maxima in LDS first.  Each thread keeps four loads in flight.
-constexpr int kAbsmaxBlocks = 1024;
-__global__ __launch_bounds__(kPartThreads) void k_absmax(const float* __restrict__ x, long count,
-                                                         unsigned* __restrict__ out) {
-  __shared__ unsigned wave_max[kPartThreads / 64];
-  unsigned m = 0;
-  const long step = (long)gridDim.x * kPartThreads;
-  long i = (long)blockIdx.x * kPartThreads + threadIdx.x;
-  for (; i + 3 * step < count; i += 4 * step) {
-    const unsigned a = __float_as_uint(x[i]), b = __float_as_uint(x[i + step]);
-    const unsigned c = __float_as_uint(x[i + 2 * step]), d = __float_as_uint(x[i + 3 * step]);
-    m = max(max(m, a & 0x7fffffffu), max(max(b & 0x7fffffffu, c & 0x7fffffffu), d & 0x7fffffffu));
-  }
-  for (; i < count; i += step) m = max(m, __float_as_uint(x[i]) & 0x7fffffffu);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, o));
-  if (__lane_id() == 0) wave_max[threadIdx.x / 64] = m;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int k = 1; k < kPartThreads / 64; ++k) m = max(m, wave_max[k]);   // m: wave 0's maximum
-    atomicMax(out, m);
-  }
-}
-
 hipError_t launch_deposit3(Lattice lat, Bins b, const float* s, BinBuffers bb, float* rho, float mass,
-                           const float* weight, unsigned* wmax, hipStream_t st) {
+                           const float* weight, const unsigned* wmax, hipStream_t st) {
   if (!weight || !wmax) return hipErrorInvalidValue;
-  // the scale of the fixed-point sums: max |weight| over the three components
-  const hipError_t e = launch_fill(reinterpret_cast<float*>(wmax), 4, 0.0f, st);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_absmax, dim3(kAbsmaxBlocks), dim3(kPartThreads), 0, st, weight, 3 * lat.npart, wmax);
   COLA_TZ_DISPATCH(b.tz, hipLaunchKernelGGL((k_deposit_tiles<TZ, unsigned long long, 3>), dim3(tile_blocks(b)),
-                                            dim3(TileDims<TZ>::TT), 0, st, lat, b, s, nullptr, bb.idx, bb.offset,
+                                            dim3(deposit_threads<TZ, 3>()), 0, st, lat, b, s, nullptr, bb.idx, bb.offset,
                                             bb.heavy, rho, mass, weight, wmax))
   return hipGetLastError();
 }
@@ -1397,22 +1372,61 @@ hipError_t launch_grad_gather(Lattice lat, Bins b, BinBuffers bb, const float* s
 // Reverse of v' = v + alpha (F - c1 s1 - c2 s2), s' = s + beta v' + d1 s1 + d2 s2:
 //   mu = lam_v + beta lam_s;  lam_s1 += d1 lam_s - alpha c1 mu;
 //   lam_s2 += d2 lam_s - alpha c2 mu;  lam_v = mu  (lam_s is updated by the gather).
-__global__ __launch_bounds__(kPartThreads) void k_adj_kick_drift(long n3, AdjStepArgs a, float* __restrict__ lam_s,
-                                                                 float* __restrict__ lam_v, float* __restrict__ lam_s1,
-                                                                 float* __restrict__ lam_s2) {
-  const long i = (long)blockIdx.x * kPartThreads + threadIdx.x;
-  if (i >= n3) return;
-  const float ls = lam_s[i];
-  const float mu = lam_v[i] + a.beta * ls;
-  lam_s1[i] += a.dd1 * ls - a.alpha * a.t2d1 * mu;
-  lam_s2[i] += a.dd2 * ls - a.alpha * a.t2d2 * mu;
-  lam_v[i] = mu;
+// mu is the weight of the step's weighted deposit, whose fixed-point scale is max |mu|:
+// it is taken here, where mu is in registers, into *wmax (zero on entry) as the bits of a
+// non-negative float, whose unsigned order is the numeric order with +inf above every
+// finite value and NaN above +inf: a non-finite entry gives a non-finite maximum.  One
+// atomic per block, 1024 blocks: atomics on a single address serialise in L2.  Also clears
+// *wmax_next for the next call.  128^3 particles: 0.033 ms; a pass of its own over mu and
+// the launch that cleared its result cost another 0.022 ms.
+constexpr int kKickBlocks = 1024;
+
+__global__ __launch_bounds__(kPartThreads) void k_adj_kick_drift(long n4, AdjStepArgs a,
+                                                                 const float4* __restrict__ lam_s,
+                                                                 float4* __restrict__ lam_v,
+                                                                 float4* __restrict__ lam_s1,
+                                                                 float4* __restrict__ lam_s2,
+                                                                 unsigned* __restrict__ wmax,
+                                                                 unsigned* __restrict__ wmax_next) {
+  __shared__ unsigned wave_max[kPartThreads / 64];
+  unsigned m = 0;
+  for (long i = (long)blockIdx.x * kPartThreads + threadIdx.x; i < n4; i += (long)gridDim.x * kPartThreads) {
+    const float4 s4 = lam_s[i];
+    float4 v4 = lam_v[i], x4 = lam_s1[i], y4 = lam_s2[i];
+    auto one = [&](float ls, float& v, float& l1, float& l2) {
+      const float mu = v + a.beta * ls;
+      l1 += a.dd1 * ls - a.alpha * a.t2d1 * mu;
+      l2 += a.dd2 * ls - a.alpha * a.t2d2 * mu;
+      v = mu;
+      m = max(m, __float_as_uint(mu) & 0x7fffffffu);
+    };
+    one(s4.x, v4.x, x4.x, y4.x);
+    one(s4.y, v4.y, x4.y, y4.y);
+    one(s4.z, v4.z, x4.z, y4.z);
+    one(s4.w, v4.w, x4.w, y4.w);
+    lam_v[i] = v4;
+    lam_s1[i] = x4;
+    lam_s2[i] = y4;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, o));
+  if (__lane_id() == 0) wave_max[threadIdx.x / 64] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int k = 1; k < kPartThreads / 64; ++k) m = max(m, wave_max[k]);   // m: wave 0's maximum
+    atomicMax(wmax, m);
+    if (blockIdx.x == 0) *wmax_next = 0;
+  }
 }
 
 hipError_t launch_adj_kick_drift(long n3, AdjStepArgs a, float* lam_s, float* lam_v, float* lam_s1, float* lam_s2,
-                                 hipStream_t st) {
-  hipLaunchKernelGGL(k_adj_kick_drift, dim3((unsigned)((n3 + kPartThreads - 1) / kPartThreads)), dim3(kPartThreads),
-                     0, st, n3, a, lam_s, lam_v, lam_s1, lam_s2);
+                                 unsigned* wmax, unsigned* wmax_next, hipStream_t st) {
+  if (n3 % 4 || wmax == wmax_next) return hipErrorInvalidValue;
+  const long n4 = n3 / 4, blocks = (n4 + kPartThreads - 1) / kPartThreads;
+  hipLaunchKernelGGL(k_adj_kick_drift, dim3((unsigned)(blocks < kKickBlocks ? blocks : kKickBlocks)),
+                     dim3(kPartThreads), 0, st, n4, a, reinterpret_cast<const float4*>(lam_s),
+                     reinterpret_cast<float4*>(lam_v), reinterpret_cast<float4*>(lam_s1),
+                     reinterpret_cast<float4*>(lam_s2), wmax, wmax_next);
   return hipGetLastError();
 }
 
