@@ -185,19 +185,18 @@ int cola_pm_force(cola_plan plan, const float *s, double a, float *acc, void *ws
  * starts from the state that call left in ws. */
 int cola_step(cola_plan plan, int32_t i, const cola_particles *p, void *ws, void *stream);
 
-/* Resident steps (off by default).  With on = 1, cola_step leaves in ws the updated
- * particle state sorted by mesh tile and its tile bins for the next step (as cola_run
- * does between its steps), and still writes s and v to the caller's arrays.  The next
- * cola_step (or cola_finish) of this plan continues from them, skipping the
- * re-binning and packing of the caller's arrays, when it is called with step index
+/* Resident steps (off by default).  With on = 1, cola_step leaves in ws a copy of the
+ * updated particle arrays and their tile bins for the next step, and still writes s and v
+ * to the caller's arrays.  The next cola_step (or cola_finish) of this plan continues from
+ * them, skipping the binning of the caller's arrays, when it is called with step index
  * i + 1 (n_steps for cola_finish), the same particle arrays and the same ws, and no
  * other call of this library has used ws in between; in every other case it starts
  * from the caller's arrays as with on = 0.  The caller must not change the particle
  * arrays (s, v, s1, s2) or ws between such calls: those changes would not be seen
  * (to change them, or to pass a new ws at the same address, call this function
  * again first: any call drops the record, so the next step starts from the arrays).
- * Results are identical bit for bit either way.  cola_run_checkpointed uses resident
- * steps internally regardless of this setting.  on = 0 or 1, else COLA_ERR_INVALID.
+ * Results are identical bit for bit either way.  cola_run_checkpointed keeps the bins
+ * between its steps in the same way regardless of this setting.  on = 0 or 1, else COLA_ERR_INVALID.
  * Host-only. */
 int cola_plan_set_resident_steps(cola_plan plan, int32_t on);
 

@@ -333,8 +333,8 @@ class Plan:
 
     def set_resident_steps(self, on: int):
         """Resident steps: consecutive step() calls on the same particles and workspace keep
-        the tile-sorted state in the workspace (the arrays must not be changed between
-        them).  0 off (default), 1 on."""
+        the particles and their tile bins in the workspace (the arrays must not be changed
+        between them).  0 off (default), 1 on."""
         _check("cola_plan_set_resident_steps", lib().cola_plan_set_resident_steps(self._c, on))
 
     def set_fft_rotation(self, on: int):

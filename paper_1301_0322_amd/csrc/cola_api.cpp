@@ -30,7 +30,7 @@ struct cola_plan_s {
   Bins bins;                      // Eulerian tiles of the force mesh
   int fft_width[2] = {0, 0};      // columns per tile of the mesh-size y passes and x pass (0: default)
   int fft_rot = -1;               // rotate the mesh-size half spectrum between y and x: 1 / 0 (-1: default)
-  // resident steps (cola_plan_set_resident_steps): what the last resident step left in
+  // resident steps (cola_plan_set_resident_steps): the copy and bins the last one left in
   // its workspace, and the workspace generation of the current call
   int resident = 0;
   uint64_t ws_gen = 0;
@@ -39,7 +39,6 @@ struct cola_plan_s {
     const void* ws = nullptr;
     const float *s = nullptr, *v = nullptr, *s1 = nullptr, *s2 = nullptr;
     int next = 0;       // the step index the state is ready for
-    int which = 0;      // sorted workspace copy holding it
     int parity = 0;     // bin buffers holding its tile counts
     uint64_t gen = 0;   // workspace generation of the call that left it
   } res;
@@ -240,18 +239,45 @@ SortedState sorted_state(cola_plan p, float* ws, int which) {
   return ss;
 }
 
-// Bins the particles at q + s (caller's Lagrangian-order arrays) by Eulerian tile and
-// deposits their CIC density (mean 1) into rho; the bins stay valid for a gather from
-// the same s.
+// The calls that start from Lagrangian-order arrays use the space of the sorted copies for
+// tile-sorted positions and forces (a float4 a particle each) and, with resident steps, a
+// copy of the particle arrays: 20 of its 26 words a particle.
+struct CallerState {
+  float4* pos;
+  float4* f;
+  SortedState keep;   // SoA, Lagrangian order
+};
+CallerState caller_state(cola_plan p, float* ws) {
+  const long n = cube(p->cfg.np);
+  float* f = sorted_state(p, ws, 0).s;
+  return {reinterpret_cast<float4*>(f), reinterpret_cast<float4*>(f + 4 * n),
+          SortedState{f + 8 * n, f + 11 * n, f + 14 * n, f + 17 * n, nullptr}};
+}
+BinBuffers pos_buffers(cola_plan p, float* ws, int parity = 0) {
+  BinBuffers bb = bin_buffers(p, ws, parity);
+  bb.pos = caller_state(p, ws).pos;
+  return bb;
+}
+
+// Bins the particles at q + s (caller's Lagrangian-order arrays) by Eulerian tile, into
+// bb.pos when it is set and else into the lists bb.idx.
+int bin_particles(cola_plan p, const float* s, const BinBuffers& bb, hipStream_t st) {
+  const Lattice lat = lattice(p);
+  COLA_HIP(traced(p, kStBinCount, st, [&] { return launch_bin_count(lat, p->bins, s, bb, st); }));
+  COLA_HIP(traced(p, kStBinScan, st, [&] { return launch_bin_scan(p->bins, bb, false, st); }));
+  return hip_status(traced(p, kStBinScatter, st, [&] {
+    return bb.pos ? launch_bin_scatter_pos(lat, bb, s, st) : launch_bin_scatter(lat, bb, st);
+  }));
+}
+
+// bin_particles, then their CIC density (mean 1) into rho; the bins stay valid for a
+// gather from the same s.
 int deposit_with(cola_plan p, const float* s, float* rho, const BinBuffers& bb, hipStream_t st) {
   const Lattice lat = lattice(p);
-  const Bins& b = p->bins;
   const double ratio = (double)lat.ratio;
-  COLA_HIP(traced(p, kStBinCount, st, [&] { return launch_bin_count(lat, b, s, bb, st); }));
-  COLA_HIP(traced(p, kStBinScan, st, [&] { return launch_bin_scan(b, bb, false, st); }));
-  COLA_HIP(traced(p, kStBinScatter, st, [&] { return launch_bin_scatter(lat, bb, st); }));
+  COLA_TRY(bin_particles(p, s, bb, st));
   COLA_HIP(traced(p, kStDeposit, st,
-                  [&] { return launch_deposit(lat, b, s, bb, rho, (float)(ratio * ratio * ratio), st); }));
+                  [&] { return launch_deposit(lat, p->bins, s, bb, rho, (float)(ratio * ratio * ratio), st); }));
   return COLA_OK;
 }
 
@@ -331,9 +357,9 @@ int fft_force(cola_plan p, double a, float* ws, hipStream_t st) {
   return COLA_OK;
 }
 
-// The force mesh of particles at q + s (binned first).
-int pm_mesh(cola_plan p, const float* s, double a, float* ws, hipStream_t st) {
-  COLA_TRY(deposit_into(p, s, ws, ws, st));
+// The force mesh of particles at q + s (binned into bb first).
+int pm_mesh(cola_plan p, const float* s, double a, float* ws, const BinBuffers& bb, hipStream_t st) {
+  COLA_TRY(deposit_with(p, s, ws, bb, st));
   return fft_force(p, a, ws, st);
 }
 
@@ -368,26 +394,6 @@ int check_particles(const cola_particles* q) {
   return COLA_OK;
 }
 
-// The caller's Lagrangian-order particles binned by tile and packed into the tile-sorted
-// workspace copy pk (slot = list position; the caller's arrays are read in order), the
-// CIC density deposited from pk and the force meshes solved: the state a cola_run step
-// starts from, so the public calls run the same deposit and gather kernels.
-int packed_mesh(cola_plan p, const cola_particles* q, double a, float* ws, hipStream_t st, SortedState& pk) {
-  const Lattice lat = lattice(p);
-  const Bins& b = p->bins;
-  const BinBuffers bb = bin_buffers(p, ws);
-  const SortedState lagr{q->s, q->v, q->s1, q->s2, nullptr};
-  pk = sorted_state(p, ws, 0);
-  const double ratio = (double)lat.ratio;
-  COLA_HIP(traced(p, kStBinCount, st, [&] { return launch_bin_count(lat, b, q->s, bb, st); }));
-  COLA_HIP(traced(p, kStBinScan, st, [&] { return launch_bin_scan(b, bb, false, st); }));
-  COLA_HIP(traced(p, kStBinScatter, st, [&] { return launch_bin_scatter_pack(lat, bb, lagr, pk, st); }));
-  COLA_HIP(traced(p, kStDeposit, st, [&] {
-    return launch_deposit(lat, b, pk.s, bb, ws, (float)(ratio * ratio * ratio), st, pk.lag);
-  }));
-  return fft_force(p, a, ws, st);
-}
-
 // Kick and drift factors of step i (eq. KDKALC) and of the closing half-kick with
 // L+(a_n) (eq. ALCtimestep, Lops).
 KickArgs step_kick(cola_plan p, const StepRow& row) {
@@ -414,89 +420,72 @@ KickArgs finish_kick(cola_plan p, const StepRow& row) {
   return k;
 }
 
-// One COLA step: PM force at a_i, merged kick, drift (eq. KDKALC).  The kick and drift
-// read the packed copy in tile order and write s, v back to the caller's arrays by
-// Lagrangian index; the arithmetic is the cola_run gather's, so both paths agree bit
-// for bit.
-int step_impl(cola_plan p, int i, const cola_particles* q, float* ws, hipStream_t st) {
-  p->res.valid = false;
-  const StepRow& row = p->table[i];
-  SortedState pk;
-  COLA_TRY(packed_mesh(p, q, row.a, ws, st, pk));
-  const KickArgs k = step_kick(p, row);
-  const GatherArgs g = gather_args(p, ws);
-  const SortedState lagr{q->s, q->v, q->s1, q->s2, nullptr};
-  return hip_status(traced(p, kStGatherKickDrift, st, [&] {
-    return launch_gather_sorted(lattice(p), p->bins, pk, lagr, bin_buffers(p, ws), kGatherKickDriftLag, g, k, st);
-  }));
-}
-
-// Resident steps.  A step that finds in the workspace the tile-sorted state and bins
-// that the previous resident step left there (same particle arrays and workspace, the
-// next step index, and no other call on that workspace since) starts from them as a
-// cola_run step does: scan and scatter of the bins, no re-binning and no packing.
-// Otherwise it bins and packs the caller's arrays.  Its gather writes the next state in
-// this step's tile order, bins it for the next step and writes s and v to the caller's
-// arrays, which are therefore current after every step.
+// Steps on Lagrangian-order arrays.  Only positions are sorted by tile (16 bytes a
+// particle) for the deposit and the force gather, which leaves the forces in Lagrangian
+// order; the kick and drift then stream over the arrays in order.  Its arithmetic is the
+// cola_run gather's, so both paths agree bit for bit.  Sorting the whole 52-byte state, to
+// kick it in tile order and write s and v back by Lagrangian index, took 0.26 ms of packing
+// and 0.46 ms of gather at 192^3 particles on 384^3 cells, against 0.06 + 0.26 + 0.10 here.
+//
+// Resident steps.  A step leaves the bins of the drifted particles for the next one (its
+// kick counts them, which saves a pass over s) and a copy of the particle arrays in the
+// workspace.  A step that finds there what the previous resident step left (same particle
+// arrays and workspace, the next step index, and no other call on that workspace since)
+// starts from them; otherwise it bins and reads the caller's arrays.  s and v are written
+// to the caller's arrays in either case, which are therefore current after every step.
 bool resident_ready(cola_plan p, int i, const cola_particles* q, const float* ws) {
   const auto& r = p->res;
   return r.valid && r.ws == ws && r.s == q->s && r.v == q->v && r.s1 == q->s1 && r.s2 == q->s2 && r.next == i &&
          (r.gen == p->ws_gen || r.gen + 1 == p->ws_gen);
 }
 
-// Deposit from the sorted state src through the bins bb, then the force meshes.
-int sorted_mesh(cola_plan p, const SortedState& src, const BinBuffers& bb, double a, float* ws, hipStream_t st) {
-  const double ratio = (double)lattice(p).ratio;
-  COLA_HIP(traced(p, kStDeposit, st, [&] {
-    return launch_deposit(lattice(p), p->bins, src.s, bb, ws, (float)(ratio * ratio * ratio), st, src.lag);
-  }));
-  return fft_force(p, a, ws, st);
-}
-
-// The sorted source of step i and its bins (clear_next: the step's gather bins for the
-// next step); which_dst and parity name the copy and bins the gather writes into.
-int resident_source(cola_plan p, int i, const cola_particles* q, float* ws, hipStream_t st, bool clear_next,
-                    BinBuffers& bb, SortedState& src, int& which_dst, int& parity) {
+// The PM force at a of the particles at q + s into f.  binned: bb already holds their tile
+// counts and keys; clear_next: the kick will count into bb.count_next.
+int lagrangian_force(cola_plan p, const float* s, double a, float* ws, const BinBuffers& bb, bool binned,
+                     bool clear_next, hipStream_t st, float4* f) {
   const Lattice lat = lattice(p);
   const Bins& b = p->bins;
-  const bool ready = resident_ready(p, i, q, ws);
-  p->res.valid = false;
-  if (ready) {
-    parity = p->res.parity;
-    bb = bin_buffers(p, ws, parity);
-    src = sorted_state(p, ws, p->res.which);
-    which_dst = p->res.which ^ 1;
-    COLA_HIP(traced(p, kStBinScan, st, [&] { return launch_bin_scan(b, bb, clear_next, st); }));
-    return hip_status(traced(p, kStBinScatter, st, [&] { return launch_bin_scatter(lat, bb, st); }));
-  }
-  parity = 0;
-  bb = bin_buffers(p, ws, 0);
-  src = sorted_state(p, ws, 0);
-  which_dst = 1;
-  const SortedState lagr{q->s, q->v, q->s1, q->s2, nullptr};
-  COLA_HIP(traced(p, kStBinCount, st, [&] { return launch_bin_count(lat, b, q->s, bb, st); }));
+  const double ratio = (double)lat.ratio;
+  if (reinterpret_cast<uintptr_t>(bb.pos) % 16 != 0) return hip_status(hipErrorInvalidValue);
+  if (!binned) COLA_HIP(traced(p, kStBinCount, st, [&] { return launch_bin_count(lat, b, s, bb, st); }));
   COLA_HIP(traced(p, kStBinScan, st, [&] { return launch_bin_scan(b, bb, clear_next, st); }));
-  return hip_status(traced(p, kStBinScatter, st, [&] { return launch_bin_scatter_pack(lat, bb, lagr, src, st); }));
+  COLA_HIP(traced(p, kStBinScatter, st, [&] { return launch_bin_scatter_pos(lat, bb, s, st); }));
+  COLA_HIP(traced(p, kStDeposit, st,
+                  [&] { return launch_deposit(lat, b, s, bb, ws, (float)(ratio * ratio * ratio), st); }));
+  COLA_TRY(fft_force(p, a, ws, st));
+  return hip_status(traced(p, kStGatherForce, st,
+                           [&] { return launch_gather_force(lat, b, bb, gather_args(p, ws), st, f); }));
+}
+
+SortedState soa(const cola_particles* q) { return SortedState{q->s, q->v, q->s1, q->s2, nullptr}; }
+
+// Step i.  binned and parity: the bins of the particles are in the buffers of that parity;
+// count: leave the next step's bins in the other ones.  src is read, q's s and v and the
+// non-null arrays of copy are written.
+int lagrangian_step(cola_plan p, int i, const SortedState& src, const cola_particles* q, const SortedState& copy,
+                    bool binned, int parity, bool count, float* ws, hipStream_t st) {
+  const StepRow& row = p->table[i];
+  const CallerState c = caller_state(p, ws);
+  const BinBuffers bb = pos_buffers(p, ws, parity);
+  COLA_TRY(lagrangian_force(p, src.s, row.a, ws, bb, binned, count, st, c.f));
+  return hip_status(traced(p, kStGatherKickDrift, st, [&] {
+    return launch_kick_drift(lattice(p), p->bins, c.f, src, soa(q), copy, step_kick(p, row), count ? &bb : nullptr, st);
+  }));
+}
+
+int step_impl(cola_plan p, int i, const cola_particles* q, float* ws, hipStream_t st) {
+  p->res.valid = false;
+  return lagrangian_step(p, i, soa(q), q, SortedState{}, false, 0, false, ws, st);
 }
 
 int resident_step(cola_plan p, int i, const cola_particles* q, float* ws, hipStream_t st) {
-  const StepRow& row = p->table[i];
-  BinBuffers bb;
-  SortedState src;
-  int which_dst, parity;
-  COLA_TRY(resident_source(p, i, q, ws, st, true, bb, src, which_dst, parity));
-  COLA_TRY(sorted_mesh(p, src, bb, row.a, ws, st));
-  const KickArgs k = step_kick(p, row);
-  GatherArgs g = gather_args(p, ws);
-  // the slot of every Lagrangian index goes to force mesh 3, free once the forces are
-  // solved, for the write-back of s and v to the caller's arrays in their order
-  g.inv = reinterpret_cast<int*>(ws + 3 * cube(p->cfg.nm));
-  const SortedState dst = sorted_state(p, ws, which_dst);
-  const Lattice lat = lattice(p);
-  COLA_HIP(traced(p, kStGatherKickDrift, st, [&] {
-    return launch_gather_sorted(lat, p->bins, src, dst, bb, kGatherKickDriftInv, g, k, st);
-  }));
-  COLA_HIP(traced(p, kStWriteback, st, [&] { return launch_writeback(lat, dst, g.inv, q->s, q->v, st); }));
+  const bool ready = resident_ready(p, i, q, ws);
+  const int parity = ready ? p->res.parity : 0;
+  p->res.valid = false;
+  const SortedState keep = caller_state(p, ws).keep;
+  SortedState copy = keep;
+  if (ready) copy.s1 = copy.s2 = nullptr;   // in place already
+  COLA_TRY(lagrangian_step(p, i, ready ? keep : soa(q), q, copy, ready, parity, true, ws, st));
   auto& r = p->res;
   r.valid = true;
   r.ws = ws;
@@ -505,44 +494,32 @@ int resident_step(cola_plan p, int i, const cola_particles* q, float* ws, hipStr
   r.s1 = q->s1;
   r.s2 = q->s2;
   r.next = i + 1;
-  r.which = which_dst;
   r.parity = parity ^ 1;
   r.gen = p->ws_gen;
   return COLA_OK;
 }
 
-// Closing half-kick at a_n and L+(a_n) (eq. ALCtimestep, Lops), as the closing step of
-// cola_run: the kick in tile order into the other workspace copy, then back to
-// Lagrangian order with L+ and the positions.  Starts from the resident state when the
-// last step left one.
-int finish_impl(cola_plan p, const cola_particles* q, float* x_out, float* v_out, float* ws, hipStream_t st) {
+// Closing half-kick at a_n and L+(a_n) (eq. ALCtimestep, Lops) on Lagrangian-order arrays;
+// binned and parity as in lagrangian_step.
+int lagrangian_finish(cola_plan p, const SortedState& src, const cola_particles* q, float* x_out, float* v_out,
+                      bool binned, int parity, float* ws, hipStream_t st) {
   const StepRow& row = p->table[p->cfg.n_steps];
-  BinBuffers bb;
-  SortedState src, out;
-  if (resident_ready(p, p->cfg.n_steps, q, ws)) {
-    int which_dst, parity;
-    COLA_TRY(resident_source(p, p->cfg.n_steps, q, ws, st, false, bb, src, which_dst, parity));
-    COLA_TRY(sorted_mesh(p, src, bb, row.a, ws, st));
-    out = sorted_state(p, ws, which_dst);
-  } else {
-    p->res.valid = false;
-    COLA_TRY(packed_mesh(p, q, row.a, ws, st, src));
-    bb = bin_buffers(p, ws);
-    out = sorted_state(p, ws, 1);
-  }
-  const KickArgs k = finish_kick(p, row);
+  const CallerState c = caller_state(p, ws);
+  COLA_TRY(lagrangian_force(p, src.s, row.a, ws, pos_buffers(p, ws, parity), binned, false, st, c.f));
   GatherArgs g = gather_args(p, ws);
   g.s = q->s;
   g.v = q->v;
-  g.s1 = q->s1;
-  g.s2 = q->s2;
   g.out_a = x_out;
   g.out_b = v_out;
-  const Lattice lat = lattice(p);
-  COLA_HIP(traced(p, kStFinish, st, [&] {
-    return launch_gather_sorted(lat, p->bins, src, out, bb, kGatherFinish, g, k, st);
-  }));
-  return hip_status(traced(p, kStUnsort, st, [&] { return launch_unsort(lat, out, g, k, st); }));
+  return hip_status(traced(p, kStFinish, st,
+                           [&] { return launch_kick_finish(lattice(p), c.f, src, g, finish_kick(p, row), st); }));
+}
+
+int finish_impl(cola_plan p, const cola_particles* q, float* x_out, float* v_out, float* ws, hipStream_t st) {
+  const bool ready = resident_ready(p, p->cfg.n_steps, q, ws);
+  const int parity = ready ? p->res.parity : 0;
+  p->res.valid = false;
+  return lagrangian_finish(p, ready ? caller_state(p, ws).keep : soa(q), q, x_out, v_out, ready, parity, ws, st);
 }
 
 // ---------------------------------------------------------------------------------
@@ -579,16 +556,6 @@ AdjLayout adj_layout(cola_plan p, float* ws) {
   return L;
 }
 
-// Bins the particles at q + s (no deposit).
-int bin_only(cola_plan p, const float* s, float* ws, hipStream_t st) {
-  const Lattice lat = lattice(p);
-  const BinBuffers bb = bin_buffers(p, ws);
-  COLA_HIP(traced(p, kStBinCount, st, [&] { return launch_bin_count(lat, p->bins, s, bb, st); }));
-  COLA_HIP(traced(p, kStBinScan, st, [&] { return launch_bin_scan(p->bins, bb, false, st); }));
-  COLA_HIP(traced(p, kStBinScatter, st, [&] { return launch_bin_scatter(lat, bb, st); }));
-  return COLA_OK;
-}
-
 // z and y forward passes over nf real fields of an n^3 grid, in place.
 int fwd_zy(cola_plan p, int stage, int n, std::initializer_list<float*> f, const float2* tw, hipStream_t st) {
   const FieldPtrs fp = fields(f);
@@ -622,14 +589,17 @@ int run_adjoint(cola_plan p, const float* w, const float* ckpt, const float* dL_
   COLA_HIP(traced(p, kStAdjKick, st, [&] { return launch_fill(reinterpret_cast<float*>(L.wmax), 4, 0.0f, st); }));
   // dL/ds at the end: derivative of the CIC density of s_n against dL/drho.
   const float* s_end = ckpt + (long)ns * n3;
-  COLA_TRY(bin_only(p, s_end, ws, st));
+  // tile-sorted positions live in the 2LPT scratch, free until the sweep is over
+  BinBuffers bb = bin_buffers(p, ws);
+  bb.pos = reinterpret_cast<float4*>(L.lpt);
+  COLA_TRY(bin_particles(p, s_end, bb, st));
   {
     AdjGatherArgs ga{};
     ga.rbar = dL_drho;
     ga.lam_s = L.lam_s;
     ga.f1 = 0.0f;
     ga.f2 = mass * inv_dx;
-    COLA_HIP(traced(p, kStAdjGather, st, [&] { return launch_grad_gather(lat, b, bin_buffers(p, ws), s_end, ga, st); }));
+    COLA_HIP(traced(p, kStAdjGather, st, [&] { return launch_grad_gather(lat, b, bb, s_end, ga, st); }));
   }
   const double kf = 2.0 * M_PI / p->cfg.box;
   for (int i = ns - 1; i >= 0; --i) {
@@ -647,9 +617,8 @@ int run_adjoint(cola_plan p, const float* w, const float* ckpt, const float* dL_
       return launch_adj_kick_drift(n3, a, L.lam_s, L.lam_v, L.lam_s1, L.lam_s2, wmax, L.wmax + ((i & 1) ^ 1), st);
     }));
     // recompute the force mesh at s_i (bins for s_i stay valid)
-    COLA_TRY(pm_mesh(p, s_i, row.a, ws, st));
+    COLA_TRY(pm_mesh(p, s_i, row.a, ws, bb, st));
     // nu_d = mass-weighted CIC deposit of mu_d = lam_v_d
-    const BinBuffers bb = bin_buffers(p, ws);
     // the three components in one particle walk (amesh[d] = amesh[0] + d nm^3)
     COLA_HIP(traced(p, kStAdjDeposit, st, [&] {
       return launch_deposit3(lat, b, s_i, bb, L.amesh[0], mass, L.lam_v, wmax, st);
@@ -958,14 +927,13 @@ int cola_pm_force(cola_plan p, const float* s, double a, float* acc, void* ws_, 
   if (!s || !acc || !(a > 0)) return COLA_ERR_INVALID;
   hipStream_t st = (hipStream_t)stream;
   float* ws = static_cast<float*>(ws_);
-  COLA_TRY(pm_mesh(p, s, a, ws, st));
+  const BinBuffers bb = pos_buffers(p, ws);
+  COLA_TRY(pm_mesh(p, s, a, ws, bb, st));
   GatherArgs g = gather_args(p, ws);
   g.s = const_cast<float*>(s);
   g.out_a = acc;
   return hip_status(
-      traced(p, kStGatherForce, st, [&] {
-        return launch_gather_force(lattice(p), p->bins, bin_buffers(p, ws), g, st);
-      }));
+      traced(p, kStGatherForce, st, [&] { return launch_gather_force(lattice(p), p->bins, bb, g, st); }));
 }
 
 int cola_step(cola_plan p, int32_t i, const cola_particles* q, void* ws_, void* stream) {
@@ -1055,16 +1023,16 @@ int cola_run_checkpointed(cola_plan p, const float* w, const cola_particles* q, 
   if (!x_out || !v_out || !ckpt) return COLA_ERR_INVALID;
   float* ws = static_cast<float*>(ws_);
   hipStream_t st = (hipStream_t)stream;
-  const size_t bytes = 3 * (size_t)cube(p->cfg.np) * sizeof(float);
+  // the kick of step i writes the checkpoint of i + 1 and bins the particles for it
+  const size_t n3 = 3 * (size_t)cube(p->cfg.np);
+  COLA_HIP(traced(p, kStCheckpoint, st,
+                  [&] { return hipMemcpyAsync(ckpt, q->s, n3 * sizeof(float), hipMemcpyDeviceToDevice, st); }));
   for (int i = 0; i < p->cfg.n_steps; ++i) {
-    float* dst = ckpt + (size_t)i * 3 * cube(p->cfg.np);
-    COLA_HIP(traced(p, kStCheckpoint, st,
-                    [&] { return hipMemcpyAsync(dst, q->s, bytes, hipMemcpyDeviceToDevice, st); }));
-    COLA_TRY(resident_step(p, i, q, ws, st));
+    SortedState copy{};
+    copy.s = ckpt + (i + 1) * n3;
+    COLA_TRY(lagrangian_step(p, i, soa(q), q, copy, i > 0, i & 1, true, ws, st));
   }
-  float* last = ckpt + (size_t)p->cfg.n_steps * 3 * cube(p->cfg.np);
-  COLA_HIP(traced(p, kStCheckpoint, st, [&] { return hipMemcpyAsync(last, q->s, bytes, hipMemcpyDeviceToDevice, st); }));
-  return finish_impl(p, q, x_out, v_out, ws, st);
+  return lagrangian_finish(p, soa(q), q, x_out, v_out, true, p->cfg.n_steps & 1, ws, st);
 }
 
 int cola_adjoint_workspace_bytes(cola_plan p, size_t* bytes) {
@@ -1230,7 +1198,7 @@ int cola_autotune(cola_plan p, const cola_particles* q, void* ws_, size_t ws_byt
         float t_min = 1e30f;
         for (int rep = 0; rep < 3 && rc == COLA_OK; ++rep) {
           rc = hip_status(hipEventRecord(e0, st));
-          if (rc == COLA_OK) rc = pm_mesh(p, q->s, p->table[0].a, ws, st);
+          if (rc == COLA_OK) rc = pm_mesh(p, q->s, p->table[0].a, ws, bin_buffers(p, ws), st);
           if (rc == COLA_OK) rc = hip_status(hipEventRecord(e1, st));
           if (rc == COLA_OK) rc = hip_status(hipEventSynchronize(e1));
           float ms = 0.f;

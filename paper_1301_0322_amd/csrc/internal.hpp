@@ -143,6 +143,7 @@ struct BinBuffers {
   int* offset;       // [count_len] exclusive prefix sum, offset[nkeys] = npart
   int* part;         // scan chunk sums
   int* heavy;        // [1 + heavy_cap] number of crowded tiles, then their indices
+  float4* pos = nullptr;   // optional [npart]: tile-sorted positions (launch_bin_scatter_pos), read instead of idx
   long count_len;
   long npart;
 };
@@ -165,6 +166,9 @@ hipError_t launch_bin_count(Lattice lat, Bins b, const float* s, BinBuffers bb, 
 // Also lists the crowded tiles (bb.heavy) for the tile kernels.
 hipError_t launch_bin_scan(Bins b, BinBuffers bb, bool clear_next, hipStream_t st);
 hipError_t launch_bin_scatter(Lattice lat, BinBuffers bb, hipStream_t st);
+// The displacement (s SoA in Lagrangian order) and Lagrangian index (bits, in w) of every
+// particle to its tile-sorted slot of bb.pos, for the kernels that take bb.
+hipError_t launch_bin_scatter_pos(Lattice lat, BinBuffers bb, const float* s, hipStream_t st);
 // Tile deposit: each tile accumulates its own particles and the boundary classes of
 // its lower neighbours that reach into it, then writes its cells with plain stores.
 // rho needs no clearing.  bb.idx lists slots of s by key.  With lag, s is a packed
@@ -193,10 +197,6 @@ enum GatherMode : int {
   kGatherKickDrift = 1,     // v += alpha (F - t2d1 s1 - t2d2 s2); s += beta v + dd1 s1 + dd2 s2, written
                             // packed in this step's tile order and binned for the next step
   kGatherFinish = 2,        // the kick only, written packed for launch_unsort (x, L+)
-  kGatherKickDriftLag = 3,  // kick and drift, s and v written to the caller's Lagrangian-order arrays
-                            // (dst SoA, by each record's Lagrangian index; no binning)
-  kGatherKickDriftInv = 4,  // kGatherKickDrift, and a.inv[Lagrangian index] = dst slot (for
-                            // launch_writeback)
 };
 struct GatherArgs {
   const float* g0;
@@ -208,11 +208,12 @@ struct GatherArgs {
   const float* s2;
   float* out_a;     // force gather: acc; launch_unsort: x
   float* out_b;     // launch_unsort: v_phys
-  int* inv;         // kGatherKickDriftInv: slot of every Lagrangian index ([n])
 };
 // Force gather (cola_pm_force): a.out_a[d n + p] = F_d of particle p of the SoA
 // displacements a.s, through the tile lists of bb.
-hipError_t launch_gather_force(Lattice lat, Bins b, BinBuffers bb, GatherArgs a, hipStream_t st);
+// With out4 the force of particle p goes to out4[p] instead (w = 0).
+hipError_t launch_gather_force(Lattice lat, Bins b, BinBuffers bb, GatherArgs a, hipStream_t st,
+                               float4* out4 = nullptr);
 
 // Particle state ordered by tile (slot j), with each particle's Lagrangian index.
 // lag == nullptr: the caller's SoA arrays s, v, s1, s2 ([3][n], slot = Lagrangian
@@ -226,27 +227,27 @@ struct SortedState {
   float* s2;
   int* lag;
 };
-// The scatter of the public step: idx becomes the identity and dst (packed) receives, at
-// each particle's tile-sorted slot, its record from the caller's Lagrangian-order SoA
-// arrays src (src.lag == nullptr).
-hipError_t launch_bin_scatter_pack(Lattice lat, BinBuffers bb, SortedState src, SortedState dst, hipStream_t st);
 // Gather + kick over the tile lists bb.idx (slots of src).  kGatherKickDrift writes
 // the kicked and drifted record of list position j to slot j of the packed dst
 // (ordered by this step's tiles) and bins it for the next step (bb.count_next,
 // bb.key_rank by dst slot); kGatherFinish writes s and the kicked v of list position
 // j as float4 j of dst.s (s.x s.y s.z v.x) and float2 j of dst.s + 4n (v.y v.z), and
-// sets dst.lag[Lagrangian index] = j, for launch_unsort.  kGatherKickDriftInv does
-// what kGatherKickDrift does and also records each record's dst slot in a.inv at its
-// Lagrangian index.
+// sets dst.lag[Lagrangian index] = j, for launch_unsort.
 hipError_t launch_gather_sorted(Lattice lat, Bins b, SortedState src, SortedState dst, BinBuffers bb, int mode,
                                 GatherArgs a, KickArgs k, hipStream_t st);
-// The caller's Lagrangian-order s and v ([3][n]) from the packed state w (a
-// kGatherKickDriftInv dst) and its inverse permutation inv.
-hipError_t launch_writeback(Lattice lat, SortedState w, const int* inv, float* s, float* v, hipStream_t st);
 // Lagrangian order from a kGatherFinish output w: a.s, a.v take s and v; a.out_a
 // x = (q + s) mod L (k.box); a.out_b v_phys = v + k.td1 a.s1 + k.td2 a.s2, the L+ of
 // the closing step (a.s1, a.s2 the caller's arrays).
 hipError_t launch_unsort(Lattice lat, SortedState w, GatherArgs a, KickArgs k, hipStream_t st);
+// The kick and drift of a step on Lagrangian-order SoA arrays with the forces f (float4 a
+// particle): src is read, s and v are written to dst (which may be src) and every non-null
+// array of copy takes its field's new value.  With count the drifted particles are binned
+// into count->key_rank and count->count_next (cleared by the step's scan).
+hipError_t launch_kick_drift(Lattice lat, Bins b, const float4* f, SortedState src, SortedState dst, SortedState copy,
+                             KickArgs k, const BinBuffers* count, hipStream_t st);
+// The closing kick in the same way: src is read, s and v go to a.s and a.v (which may be
+// src's), x and v_phys to a.out_a and a.out_b as in launch_unsort.
+hipError_t launch_kick_finish(Lattice lat, const float4* f, SortedState src, GatherArgs a, KickArgs k, hipStream_t st);
 
 // Adjoint kernels.
 struct AdjGatherArgs {

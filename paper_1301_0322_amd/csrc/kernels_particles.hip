@@ -356,32 +356,30 @@ __global__ __launch_bounds__(kPartThreads) void k_bin_scatter(long npart, const 
   }
 }
 
-// The scatter of the public step: besides its list entry (the identity: slot j holds the
-// particle listed at j), each particle's record is written packed to its tile-sorted slot
-// j = offset[key] + rank from the caller's Lagrangian-order arrays, which are read in
-// order; a wave's particles share few keys, so its writes land in runs of slots.
-__global__ __launch_bounds__(kPartThreads) void k_bin_scatter_pack(long npart, const int2* __restrict__ key_rank,
-                                                                   const int* __restrict__ offset,
-                                                                   int* __restrict__ idx, SortedState src,
-                                                                   SortedState dst) {
-  const long p = (long)blockIdx.x * kPartThreads + threadIdx.x;
-  if (p >= npart) return;
-  const int2 kr = key_rank[p];
-  const long j = offset[kr.x] + kr.y;
-  float a[12];
+// The scatter of the calls that start from Lagrangian-order displacements and read every
+// particle's position more than once: the position and the Lagrangian index (bits) of a
+// particle go to its tile-sorted slot as one float4, so that deposit and gather read
+// consecutive slots and need no list.
+template <int U>
+__global__ __launch_bounds__(kPartThreads) void k_bin_scatter_pos(long npart, const int2* __restrict__ key_rank,
+                                                                  const int* __restrict__ offset,
+                                                                  const float* __restrict__ s,
+                                                                  float4* __restrict__ pos) {
+  const long p0 = (long)blockIdx.x * (U * kPartThreads) + threadIdx.x;
+  int2 kr[U];
+  float sv[U][3];
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    a[d] = src.s[d * npart + p];
-    a[3 + d] = src.v[d * npart + p];
-    a[6 + d] = src.s1[d * npart + p];
-    a[9 + d] = src.s2[d * npart + p];
+  for (int u = 0; u < U; ++u) {
+    const long p = min(p0 + u * kPartThreads, npart - 1);
+    kr[u] = key_rank[p];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) sv[u][d] = s[d * npart + p];
   }
-  float4* q = reinterpret_cast<float4*>(dst.s);
-  q[j] = make_float4(a[0], a[1], a[2], a[3]);
-  q[npart + j] = make_float4(a[4], a[5], a[6], a[7]);
-  q[2 * npart + j] = make_float4(a[8], a[9], a[10], a[11]);
-  dst.lag[j] = (int)p;
-  idx[j] = (int)j;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const long p = p0 + u * kPartThreads;
+    if (p < npart) pos[offset[kr[u].x] + kr[u].y] = make_float4(sv[u][0], sv[u][1], sv[u][2], __int_as_float((int)p));
+  }
 }
 
 struct TileGeom {
@@ -445,14 +443,12 @@ __device__ __forceinline__ bool tile_is_listed(const Lattice& lat, const Bins& b
   return own > heavy_min_of(lat.npart, b.heavy_cap);
 }
 
-// Tile-local stencil of the particle in slot `slot` of s with Lagrangian index `lagi`;
+// Tile-local stencil of the particle with displacement sv and Lagrangian index `lagi`;
 // false if its base cell is not in this tile (never the case: binning used the same
 // arithmetic).
 template <int TZ>
-__device__ __forceinline__ bool local_stencil(const Lattice& lat, const TileGeom& g, const float* s, unsigned slot,
-                                              unsigned lagi, float sv[3], int lc[3], float fr[3]) {
-#pragma unroll
-  for (int d = 0; d < 3; ++d) sv[d] = s[d * lat.npart + slot];
+__device__ __forceinline__ bool local_stencil(const Lattice& lat, const TileGeom& g, unsigned lagi, const float sv[3],
+                                              int lc[3], float fr[3]) {
   const Stencil st = stencil_of(lat, lagi, sv);
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
@@ -606,7 +602,9 @@ __device__ __forceinline__ void interpolate3(const float* tile, const float* con
 //   and weighted ones scaled by the power of two that wmax gives).
 // idx holds slots of s; with lag (optional) s is a packed state (positions in the
 // first float4 of each slot) and lag maps a slot to its Lagrangian index; without,
-// s is SoA [3][np^3] in Lagrangian order.  weight is indexed by Lagrangian index.
+// s is SoA [3][np^3] in Lagrangian order.  With pos (tile-sorted positions,
+// k_bin_scatter_pos) slots are list positions, and s, lag and idx are not read.  weight is
+// indexed by Lagrangian index.
 constexpr int kDepRanges = 10;
 // Range r: neighbour mask, first class position and the position past the last, four bits
 // a range (r = 0 the tile itself, then x, y, z, z, xy, yz, yz, xz, xyz).
@@ -624,6 +622,7 @@ template <int TZ, class ACC, int NW = 1>
 __global__ __launch_bounds__((deposit_threads<TZ, NW>())) void k_deposit_tiles(Lattice lat, Bins bins, const float* __restrict__ s,
                                                                 const int* __restrict__ lag,
                                                                 const int* __restrict__ idx,
+                                                                const float4* __restrict__ pos,
                                                                 const int* __restrict__ offset,
                                                                 const int* __restrict__ heavy, float* __restrict__ rho,
                                                                 float mass, const float* __restrict__ weight,
@@ -709,7 +708,16 @@ __global__ __launch_bounds__((deposit_threads<TZ, NW>())) void k_deposit_tiles(L
         for (int q = 1; q < kDepRanges; ++q) r += (rpre[q] <= ii) ? 1 : 0;
       }
       msk[u] = rmask[r];
-      const unsigned slot = in[u] ? (unsigned)idx[rbeg[r] + ii - rpre[r]] : 0u;
+      const unsigned at = in[u] ? (unsigned)(rbeg[r] + ii - rpre[r]) : 0u;
+      if (pos) {   // tile-sorted positions with the Lagrangian index
+        const float4 a = pos[at];
+        lg[u] = __float_as_uint(a.w);
+        sv[u][0] = a.x;
+        sv[u][1] = a.y;
+        sv[u][2] = a.z;
+        continue;
+      }
+      const unsigned slot = in[u] ? (unsigned)idx[at] : 0u;
       if (lag) {   // packed state: positions in the first float4 of the slot
         lg[u] = (unsigned)lag[slot];
         const float4 a = reinterpret_cast<const float4*>(s)[slot];
@@ -789,10 +797,31 @@ __global__ __launch_bounds__((deposit_threads<TZ, NW>())) void k_deposit_tiles(L
 // Lagrangian-order displacements (cola_pm_force).  The kick and drift gathers are
 // k_gather_sorted's.
 // ---------------------------------------------------------------------------------
+// The particle at list position i: slot through idx into the SoA displacements s, or with
+// pos (tile-sorted positions) directly.
+__device__ __forceinline__ unsigned listed_particle(const float* s, long n, const int* idx, const float4* pos, int i,
+                                                    float sv[3]) {
+  if (pos) {
+    const float4 a = pos[i];
+    sv[0] = a.x;
+    sv[1] = a.y;
+    sv[2] = a.z;
+    return __float_as_uint(a.w);
+  }
+  const unsigned p = (unsigned)idx[i];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) sv[d] = s[d * n + p];
+  return p;
+}
+
+// Outputs by Lagrangian index: g.out_a ([3][np^3]), or with out4 one float4 a particle
+// (one scattered 16-byte store instead of three of 4 bytes).
 template <int TZ>
 __global__ __launch_bounds__(TileDims<TZ>::TT) void k_gather_tiles(Lattice lat, Bins bins, const int* __restrict__ idx,
+                                                               const float4* __restrict__ pos,
                                                                const int* __restrict__ offset,
-                                                               const int* __restrict__ heavy, GatherArgs g) {
+                                                               const int* __restrict__ heavy, GatherArgs g,
+                                                               float4* __restrict__ out4) {
   using D = TileDims<TZ>;
   __shared__ __align__(16) float tile[3 * D::EXT];
   TileGeom t;
@@ -800,19 +829,28 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_gather_tiles(Lattice lat, 
   if (!tile_geom<TZ>(bins, heavy, t, listed)) return;
   const int beg = offset[(long)t.bin * kClasses], end = offset[(long)(t.bin + 1) * kClasses];
   if (!listed && tile_is_listed(lat, bins, end - beg)) return;
+  const long n = lat.npart;
   const float* gf[3] = {g.g0, g.g1, g.g2};
+  // the first batch's positions are in flight together with the force tile
+  float sv[3] = {0.f, 0.f, 0.f};
+  unsigned p = 0;
+  const int first = beg + (int)threadIdx.x;
+  if (first < end) p = listed_particle(g.s, n, idx, pos, first, sv);
   stage_fields<TZ, 3>(t, lat.nm, gf, tile);
   __syncthreads();
-  const long n = lat.npart;
-  for (int i = beg + threadIdx.x; i < end; i += D::TT) {
-    const unsigned p = (unsigned)idx[i];
-    float sv[3], fr[3];
+  for (int i = first; i < end; i += D::TT) {
+    if (i != first) p = listed_particle(g.s, n, idx, pos, i, sv);
+    float fr[3];
     int lc[3];
-    if (!local_stencil<TZ>(lat, t, g.s, p, p, sv, lc, fr)) continue;   // cannot happen
+    if (!local_stencil<TZ>(lat, t, p, sv, lc, fr)) continue;   // cannot happen
     float f[3] = {0.f, 0.f, 0.f};
     interpolate3<TZ>(tile, gf, t, lc, fr, lat.nm, f);
+    if (out4) {
+      out4[p] = make_float4(f[0], f[1], f[2], 0.f);
+    } else {
 #pragma unroll
-    for (int d = 0; d < 3; ++d) g.out_a[d * n + p] = f[d];
+      for (int d = 0; d < 3; ++d) g.out_a[d * n + p] = f[d];
+    }
   }
 }
 
@@ -827,6 +865,7 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_gather_tiles(Lattice lat, 
 // ---------------------------------------------------------------------------------
 template <int TZ>
 __global__ __launch_bounds__(TileDims<TZ>::TT) void k_grad_gather(Lattice lat, Bins bins, const int* __restrict__ idx,
+                                                              const float4* __restrict__ pos,
                                                               const int* __restrict__ offset,
                                                               const int* __restrict__ heavy,
                                                               const float* __restrict__ s, AdjGatherArgs ga) {
@@ -848,10 +887,10 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_grad_gather(Lattice lat, B
   __syncthreads();
   const long n = lat.npart;
   for (int i = beg + threadIdx.x; i < end; i += D::TT) {
-    const unsigned p = (unsigned)idx[i];
     float sv[3], fr[3];
     int lc[3];
-    if (!local_stencil<TZ>(lat, t, s, p, p, sv, lc, fr)) continue;   // cannot happen
+    const unsigned p = listed_particle(s, n, idx, pos, i, sv);
+    if (!local_stencil<TZ>(lat, t, p, sv, lc, fr)) continue;   // cannot happen
     float mu[3] = {0.f, 0.f, 0.f};
     if (with_g) {
 #pragma unroll
@@ -997,7 +1036,7 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_gather_sorted(Lattice lat,
   if (beg < end) load_record(src, n, idx[min(beg + (int)threadIdx.x, end - 1)], r);
   const float* gf[3] = {g.g0, g.g1, g.g2};
   stage_fields<TZ, 3>(t, lat.nm, gf, tile);
-  constexpr bool BINS = MODE == kGatherKickDrift || MODE == kGatherKickDriftInv;
+  constexpr bool BINS = MODE == kGatherKickDrift;
   __syncthreads();
   for (int base = beg; base < end; base += D::TT) {   // block-uniform trip count
     const int j = base + threadIdx.x;
@@ -1022,15 +1061,6 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_gather_sorted(Lattice lat,
         if constexpr (MODE != kGatherFinish) snew[d] = r.s[d] + k.beta * v + k.dd1 * a1 + k.dd2 * a2;
         vf[d] = v;
       }
-      if constexpr (MODE == kGatherKickDriftLag) {
-        // the caller's Lagrangian-order arrays (when src is the same arrays, each
-        // particle is read and written by one lane)
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          dst.s[d * n + r.lag] = snew[d];
-          dst.v[d * n + r.lag] = vf[d];
-        }
-      }
       if constexpr (MODE == kGatherFinish) {
         // finish: s and the kicked v, in this step's tile order, as a float4 plane
         // (s.x s.y s.z v.x) and a float2 plane (v.y v.z), and the slot of every
@@ -1046,7 +1076,6 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_gather_sorted(Lattice lat,
       const int rank = wave_rank_grouped(in, key, count_next, pos);
       if (in) {
         const int slot = j - (int)__lane_id() + pos;   // a wave's active lanes are its first ones
-        if constexpr (MODE == kGatherKickDriftInv) g.inv[r.lag] = slot;
         float4* q = reinterpret_cast<float4*>(dst.s);
         q[slot] = make_float4(snew[0], snew[1], snew[2], vf[0]);
         q[n + slot] = make_float4(vf[1], vf[2], r.s1[0], r.s1[1]);
@@ -1211,10 +1240,13 @@ hipError_t launch_bin_scan(Bins b, BinBuffers bb, bool clear_next, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t launch_bin_scatter_pack(Lattice lat, BinBuffers bb, SortedState src, SortedState dst, hipStream_t st) {
-  if (src.lag || !dst.s || !dst.lag || reinterpret_cast<uintptr_t>(dst.s) % 16 != 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_bin_scatter_pack, dim3(part_blocks(lat.npart)), dim3(kPartThreads), 0, st, lat.npart,
-                     bb.key_rank, bb.offset, bb.idx, src, dst);
+hipError_t launch_bin_scatter_pos(Lattice lat, BinBuffers bb, const float* s, hipStream_t st) {
+  if (!bb.pos) return hipErrorInvalidValue;
+  const dim3 grid(bin_blocks(lat.npart)), block(kPartThreads);
+  if (bin_per(lat.npart) > 1)
+    hipLaunchKernelGGL(k_bin_scatter_pos<kBinPer>, grid, block, 0, st, lat.npart, bb.key_rank, bb.offset, s, bb.pos);
+  else
+    hipLaunchKernelGGL(k_bin_scatter_pos<1>, grid, block, 0, st, lat.npart, bb.key_rank, bb.offset, s, bb.pos);
   return hipGetLastError();
 }
 
@@ -1231,22 +1263,22 @@ hipError_t launch_deposit3(Lattice lat, Bins b, const float* s, BinBuffers bb, f
                            const float* weight, const unsigned* wmax, hipStream_t st) {
   if (!weight || !wmax) return hipErrorInvalidValue;
   COLA_TZ_DISPATCH(b.tz, hipLaunchKernelGGL((k_deposit_tiles<TZ, unsigned long long, 3>), dim3(tile_blocks(b)),
-                                            dim3(deposit_threads<TZ, 3>()), 0, st, lat, b, s, nullptr, bb.idx, bb.offset,
-                                            bb.heavy, rho, mass, weight, wmax))
+                                            dim3(deposit_threads<TZ, 3>()), 0, st, lat, b, s, nullptr, bb.idx, bb.pos,
+                                            bb.offset, bb.heavy, rho, mass, weight, wmax))
   return hipGetLastError();
 }
 
 hipError_t launch_deposit(Lattice lat, Bins b, const float* s, BinBuffers bb, float* rho, float mass,
                           hipStream_t st, const int* lag) {
   COLA_TZ_DISPATCH(b.tz, hipLaunchKernelGGL((k_deposit_tiles<TZ, unsigned long long>), dim3(tile_blocks(b)),
-                                            dim3(TileDims<TZ>::TT), 0, st, lat, b, s, lag, bb.idx, bb.offset, bb.heavy, rho,
-                                            mass, nullptr, nullptr))
+                                            dim3(TileDims<TZ>::TT), 0, st, lat, b, s, lag, bb.idx, bb.pos, bb.offset, bb.heavy,
+                                            rho, mass, nullptr, nullptr))
   return hipGetLastError();
 }
 
-hipError_t launch_gather_force(Lattice lat, Bins b, BinBuffers bb, GatherArgs a, hipStream_t st) {
+hipError_t launch_gather_force(Lattice lat, Bins b, BinBuffers bb, GatherArgs a, hipStream_t st, float4* out4) {
   COLA_TZ_DISPATCH(b.tz, hipLaunchKernelGGL(k_gather_tiles<TZ>, dim3(tile_blocks(b)), dim3(TileDims<TZ>::TT), 0, st,
-                                            lat, b, bb.idx, bb.offset, bb.heavy, a));
+                                            lat, b, bb.idx, bb.pos, bb.offset, bb.heavy, a, out4));
   return hipGetLastError();
 }
 
@@ -1257,12 +1289,6 @@ static void gather_sorted_tz(Lattice lat, Bins b, SortedState src, SortedState d
   if (mode == kGatherKickDrift)
     hipLaunchKernelGGL((k_gather_sorted<TZ, kGatherKickDrift>), grid, block, 0, st, lat, b, src, dst, bb.idx,
                        bb.offset, bb.heavy, a, k, bb.key_rank, bb.count_next);
-  else if (mode == kGatherKickDriftInv)
-    hipLaunchKernelGGL((k_gather_sorted<TZ, kGatherKickDriftInv>), grid, block, 0, st, lat, b, src, dst, bb.idx,
-                       bb.offset, bb.heavy, a, k, bb.key_rank, bb.count_next);
-  else if (mode == kGatherKickDriftLag)
-    hipLaunchKernelGGL((k_gather_sorted<TZ, kGatherKickDriftLag>), grid, block, 0, st, lat, b, src, dst, bb.idx,
-                       bb.offset, bb.heavy, a, k, bb.key_rank, bb.count_next);
   else
     hipLaunchKernelGGL((k_gather_sorted<TZ, kGatherFinish>), grid, block, 0, st, lat, b, src, dst, bb.idx, bb.offset, bb.heavy,
                        a, k, bb.key_rank, bb.count_next);
@@ -1270,14 +1296,8 @@ static void gather_sorted_tz(Lattice lat, Bins b, SortedState src, SortedState d
 
 hipError_t launch_gather_sorted(Lattice lat, Bins b, SortedState src, SortedState dst, BinBuffers bb, int mode,
                                 GatherArgs a, KickArgs k, hipStream_t st) {
-  if (mode != kGatherKickDrift && mode != kGatherFinish && mode != kGatherKickDriftLag &&
-      mode != kGatherKickDriftInv)
-    return hipErrorInvalidValue;
-  if (mode == kGatherKickDriftInv && !a.inv) return hipErrorInvalidValue;
-  if (mode == kGatherKickDriftLag) {
-    // dst is the caller's SoA arrays (s, v) in Lagrangian order
-    if (!dst.s || !dst.v || dst.lag) return hipErrorInvalidValue;
-  } else if (!dst.s || !dst.lag || reinterpret_cast<uintptr_t>(dst.s) % 16 != 0) {
+  if (mode != kGatherKickDrift && mode != kGatherFinish) return hipErrorInvalidValue;
+  if (!dst.s || !dst.lag || reinterpret_cast<uintptr_t>(dst.s) % 16 != 0) {
     // dst is packed: 12 n floats from dst.s, 16-byte aligned, and n ints of lag
     return hipErrorInvalidValue;
   }
@@ -1309,31 +1329,17 @@ __device__ __forceinline__ long unsort_index(const Lattice& lat) {
   return (long)blockIdx.x * kPartThreads + threadIdx.x;
 }
 
-__global__ __launch_bounds__(kPartThreads) void k_writeback(Lattice lat, const float4* __restrict__ w,
-                                                            const int* __restrict__ inv, float* __restrict__ s,
-                                                            float* __restrict__ v) {
-  const long n = lat.npart;
-  const long p = unsort_index(lat);
-  if (p >= n) return;
-  const long j = inv[p];
-  const float4 a = w[j], b = w[n + j];   // (s.x s.y s.z v.x), (v.y v.z s1.x s1.y)
-  s[p] = a.x;
-  s[n + p] = a.y;
-  s[2 * n + p] = a.z;
-  v[p] = a.w;
-  v[n + p] = b.x;
-  v[2 * n + p] = b.y;
-}
-
-hipError_t launch_writeback(Lattice lat, SortedState w, const int* inv, float* s, float* v, hipStream_t st) {
-  if (!w.s || !inv || !s || !v || reinterpret_cast<uintptr_t>(w.s) % 16 != 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_writeback, dim3(part_blocks(lat.npart)), dim3(kPartThreads), 0, st, lat,
-                     reinterpret_cast<const float4*>(w.s), inv, s, v);
-  return hipGetLastError();
+// Component d of the outputs of particle p: x = (q + s) mod L and v_phys (eq. Lops).
+__device__ __forceinline__ void closing_outputs(const Lattice& lat, const GatherArgs& g, const KickArgs& k, long p,
+                                                int d, int li, float s, float v, float s1, float s2) {
+  g.out_b[d * lat.npart + p] = v + k.td1 * s1 + k.td2 * s2;
+  float x = (float)li * (k.box / (float)lat.np) + s;
+  x = x - k.box * floorf(x / k.box);
+  if (x >= k.box) x -= k.box;
+  g.out_a[d * lat.npart + p] = x;
 }
 
 __global__ __launch_bounds__(kPartThreads) void k_unsort(Lattice lat, SortedState w, GatherArgs g, KickArgs k) {
-  const int np = lat.np;
   const long n = lat.npart;
   const long p = unsort_index(lat);
   if (p >= n) return;
@@ -1347,11 +1353,7 @@ __global__ __launch_bounds__(kPartThreads) void k_unsort(Lattice lat, SortedStat
   for (int d = 0; d < 3; ++d) {
     g.s[d * n + p] = sv[d];
     g.v[d * n + p] = vv[d];
-    g.out_b[d * n + p] = vv[d] + k.td1 * g.s1[d * n + p] + k.td2 * g.s2[d * n + p];
-    float x = (float)li[d] * (k.box / (float)np) + sv[d];
-    x = x - k.box * floorf(x / k.box);
-    if (x >= k.box) x -= k.box;
-    g.out_a[d * n + p] = x;
+    closing_outputs(lat, g, k, p, d, li[d], sv[d], vv[d], g.s1[d * n + p], g.s2[d * n + p]);
   }
 }
 
@@ -1360,9 +1362,90 @@ hipError_t launch_unsort(Lattice lat, SortedState w, GatherArgs a, KickArgs k, h
   return hipGetLastError();
 }
 
+// Kick and drift of one particle per thread in Lagrangian order, its force in f (one float4
+// a particle, k_gather_tiles): the public step, whose arrays are read and written in order.
+// The arithmetic is k_gather_sorted's.  src is read, s and v go to dst and, where given, to
+// the copies cs and cv; s1 and s2 to c1 and c2 when given.  With COUNT the drifted particle
+// is binned for the next step on the way (k_bin_count without its pass over s).
+template <int TZ, bool COUNT>
+__global__ __launch_bounds__(kPartThreads) void k_kick_drift(Lattice lat, Bins bins, const float4* __restrict__ f,
+                                                             SortedState src, SortedState dst, SortedState copy,
+                                                             KickArgs k, int2* __restrict__ key_rank,
+                                                             int* __restrict__ count) {
+  const long n = lat.npart;
+  const long i = xcd_block(gridDim.x) * kPartThreads + threadIdx.x;
+  const bool in = i < n;
+  int bin = 0;
+  if (in) {
+    const float4 f4 = f[i];
+    const float fv[3] = {f4.x, f4.y, f4.z};
+    float snew[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const long j = d * n + i;
+      const float a1 = src.s1[j], a2 = src.s2[j];
+      const float v = src.v[j] + k.alpha * (fv[d] - k.t2d1 * a1 - k.t2d2 * a2);
+      snew[d] = src.s[j] + k.beta * v + k.dd1 * a1 + k.dd2 * a2;
+      dst.s[j] = snew[d];
+      dst.v[j] = v;
+      if (copy.s) copy.s[j] = snew[d];
+      if (copy.v) copy.v[j] = v;
+      if (copy.s1) copy.s1[j] = a1;
+      if (copy.s2) copy.s2[j] = a2;
+    }
+    if constexpr (COUNT) bin = key_of<TZ>(bins, stencil_of(lat, (unsigned)i, snew).c);
+  }
+  if constexpr (COUNT) {
+    const WaveGroup g = wave_group(in, bin);
+    const int rank = wave_settle(wave_reserve(in, bin, g, count), g);
+    if (in) key_rank[i] = make_int2(bin, rank);
+  }
+}
+
+hipError_t launch_kick_drift(Lattice lat, Bins b, const float4* f, SortedState src, SortedState dst, SortedState copy,
+                             KickArgs k, const BinBuffers* count, hipStream_t st) {
+  if (src.lag || dst.lag || copy.lag) return hipErrorInvalidValue;
+  const dim3 grid((part_blocks(lat.npart) + kXcds - 1) / kXcds * kXcds), block(kPartThreads);
+  if (!count) {
+    hipLaunchKernelGGL((k_kick_drift<8, false>), grid, block, 0, st, lat, b, f, src, dst, copy, k, nullptr, nullptr);
+    return hipGetLastError();
+  }
+  COLA_TZ_DISPATCH(b.tz, hipLaunchKernelGGL((k_kick_drift<TZ, true>), grid, block, 0, st, lat, b, f, src, dst, copy, k,
+                                            count->key_rank, count->count_next));
+  return hipGetLastError();
+}
+
+// The closing kick in the same way, then x and v_phys (eq. Lops) as k_unsort forms them.
+// src is read, s and v go to g.s and g.v.
+__global__ __launch_bounds__(kPartThreads) void k_kick_finish(Lattice lat, const float4* __restrict__ f,
+                                                              SortedState src, GatherArgs g, KickArgs k) {
+  const long n = lat.npart;
+  const long i = (long)blockIdx.x * kPartThreads + threadIdx.x;
+  if (i >= n) return;
+  const float4 f4 = f[i];
+  const float fv[3] = {f4.x, f4.y, f4.z};
+  int li[3];
+  lag_index(lat, (unsigned)i, li);
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const long j = d * n + i;
+    const float s = src.s[j], a1 = src.s1[j], a2 = src.s2[j];
+    const float v = src.v[j] + k.alpha * (fv[d] - k.t2d1 * a1 - k.t2d2 * a2);
+    if (g.s != src.s) g.s[j] = s;
+    g.v[j] = v;
+    closing_outputs(lat, g, k, i, d, li[d], s, v, a1, a2);
+  }
+}
+
+hipError_t launch_kick_finish(Lattice lat, const float4* f, SortedState src, GatherArgs a, KickArgs k, hipStream_t st) {
+  if (src.lag) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_kick_finish, dim3(part_blocks(lat.npart)), dim3(kPartThreads), 0, st, lat, f, src, a, k);
+  return hipGetLastError();
+}
+
 hipError_t launch_grad_gather(Lattice lat, Bins b, BinBuffers bb, const float* s, AdjGatherArgs ga, hipStream_t st) {
   COLA_TZ_DISPATCH(b.tz, hipLaunchKernelGGL(k_grad_gather<TZ>, dim3(tile_blocks(b)), dim3(TileDims<TZ>::TT), 0, st, lat, b,
-                                            bb.idx, bb.offset, bb.heavy, s, ga));
+                                            bb.idx, bb.pos, bb.offset, bb.heavy, s, ga));
   return hipGetLastError();
 }
 
