@@ -20,6 +20,7 @@
 // from the host's FP64 table in LDS.
 #pragma once
 
+#include <type_traits>
 #include <utility>
 
 #include "fft_device.hpp"
@@ -131,7 +132,7 @@ __device__ __forceinline__ float2 tw_table(const float2* tab, int e) {
   return w;
 }
 
-template <int L_, int NT_, bool ROW_>
+template <int L_, int NT_, bool ROW_, bool SPLIT_ = false>
 struct Pencil {
   static constexpr int L = L_, NT = NT_;
   static constexpr bool ROW = ROW_;
@@ -149,6 +150,11 @@ struct Pencil {
   static constexpr bool CHUNK = !ROW && UB > 1;
   static constexpr int PC = round_up(R1 * NT, 32) + NT;
   static constexpr int LDS = ROW ? NT * pmax(SF, SI) : (CHUNK ? R1 * PC : R1 * PF);
+  // Split exchange: real and imaginary parts go through the LDS one after the other, which
+  // halves the LDS of the exchange for two more barriers.
+  static constexpr bool SPLIT = SPLIT_;
+  static_assert(!(SPLIT && CHUNK), "a chunked exchange is not split");
+  using Ex = std::conditional_t<SPLIT, float, float2>;
 
   static_assert(R2 > 0 && R1 * R2 == L, "unsupported transform length");
   static_assert(R1 <= 32 && R2 <= 32, "register DFTs are at most 32 long");
@@ -246,7 +252,7 @@ struct Pencil {
   // Destroys a.  The caller has the LDS exchange free on entry (a barrier since its last
   // reads) and the twiddle table visible; returns without a trailing barrier.
   template <int S, int TWS>
-  __device__ static void fwd_like(float2 (&a)[R2], float2 (&q)[UB][R1], float2* ex, const float2* tab) {
+  __device__ static void fwd_like(float2 (&a)[R2], float2 (&q)[UB][R1], Ex* ex, const float2* tab) {
     int b, i1;
     a_unit(b, i1);
     dft_reg<R2, S>(a);
@@ -264,6 +270,29 @@ struct Pencil {
         if (!b_unit(u, bb, j2)) continue;
 #pragma unroll
         for (int k = 0; k < R1; ++k) q[u][k] = ex[k * PC + (j2 - u * R1) * NT + bb];
+        dft_reg<R1, S>(q[u]);
+      }
+    } else if constexpr (SPLIT) {
+#pragma unroll
+      for (int j2 = 0; j2 < R2; ++j2) ex[addr_f(b, i1, j2)] = a[j2].x;
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        int bb, j2;
+        if (!b_unit(u, bb, j2)) continue;
+#pragma unroll
+        for (int k = 0; k < R1; ++k) q[u][k].x = ex[addr_f(bb, k, j2)];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int j2 = 0; j2 < R2; ++j2) ex[addr_f(b, i1, j2)] = a[j2].y;
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        int bb, j2;
+        if (!b_unit(u, bb, j2)) continue;
+#pragma unroll
+        for (int k = 0; k < R1; ++k) q[u][k].y = ex[addr_f(bb, k, j2)];
         dft_reg<R1, S>(q[u]);
       }
     } else {
@@ -284,7 +313,7 @@ struct Pencil {
   // B-layout (positions j2 + R2 j1) -> A-layout (positions b2 + R1 b1), sign S.
   // Destroys q.  Same LDS contract as fwd_like.
   template <int S, int TWS>
-  __device__ static void inv_like(float2 (&q)[UB][R1], float2 (&a)[R2], float2* ex, const float2* tab) {
+  __device__ static void inv_like(float2 (&q)[UB][R1], float2 (&a)[R2], Ex* ex, const float2* tab) {
 #pragma unroll
     for (int u = 0; u < UB; ++u) {
       int b, j2;
@@ -309,6 +338,28 @@ struct Pencil {
         for (int jj = 0; jj < R1; ++jj)
           if (u * R1 + jj < R2) a[u * R1 + jj] = ex[b2 * PC + jj * NT + b];
       }
+    } else if constexpr (SPLIT) {
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        int bu, j2;
+        if (!b_unit(u, bu, j2)) continue;
+#pragma unroll
+        for (int k = 0; k < R1; ++k) ex[addr_i(bu, j2, k)] = q[u][k].x;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int j2 = 0; j2 < R2; ++j2) a[j2].x = ex[addr_i(b, j2, b2)];
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        int bu, j2;
+        if (!b_unit(u, bu, j2)) continue;
+#pragma unroll
+        for (int k = 0; k < R1; ++k) ex[addr_i(bu, j2, k)] = q[u][k].y;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int j2 = 0; j2 < R2; ++j2) a[j2].y = ex[addr_i(b, j2, b2)];
     } else {
 #pragma unroll
       for (int u = 0; u < UB; ++u) {

@@ -67,6 +67,18 @@ constexpr int col_width_default() {
   return col_ok<N, 16>() ? 16 : col_ok<N, 8>() ? 8 : 4;
 }
 
+// Tiles of the single and paired column passes.  At 384 and 1024 the exchange (52 and
+// 135 KB) leaves two blocks and one to a CU; split it leaves five and two, and those passes
+// do not need the registers that would cap them lower.  384 (steps of 192^3
+// particles): pair 0.197 -> 0.159 ms, inverse 0.110 -> 0.098, forward 0.076 -> 0.073.  1024:
+// forward 1.78 -> 1.66 ms, inverse 1.81 -> 1.74.  At 256, 512 and 768 it measured no gain,
+// nor in the x passes, whose registers set their residency (384: 0.215 -> 0.232 ms), nor in
+// the one-block pair at 1024.
+template <int N, int B>
+using ColPencil = Pencil<N, B, false, N == 384 || N == 1024>;
+template <int N, int B>
+using PairPencil = Pencil<N, B, false, N == 384>;
+
 // Stored row of logical row y of x-plane x in a rotated half spectrum.
 template <int N>
 __device__ __forceinline__ int rot_row(int y, int x, int rot) {
@@ -112,7 +124,7 @@ template <int N>
 __global__ __launch_bounds__(ZPencil<N>::T) void k_zfwd(FieldPtrs in, FieldPtrs out, const float2* __restrict__ tw) {
   using P = ZPencil<N>;
   constexpr int M = N / 2;
-  __shared__ __align__(16) float2 ex[P::LDS];
+  __shared__ __align__(16) typename P::Ex ex[P::LDS];
   __shared__ float2 stw_l[z_stw_len<N>()];
   const long row0 = (long)blockIdx.x * P::NT;
   float2 a[P::R2];
@@ -147,7 +159,7 @@ __global__ __launch_bounds__(ZPencil<N>::T) void k_zfwd(FieldPtrs in, FieldPtrs 
 // ---------------------------------------------------------------------------------
 // Pre-processing of loaded B-layout registers, then the inverse half-length transform.
 template <class P, int N>
-__device__ __forceinline__ void zinv_regs(float2 (&q)[P::UB][P::R1], float2 (&a)[P::R2], float2* ex,
+__device__ __forceinline__ void zinv_regs(float2 (&q)[P::UB][P::R1], float2 (&a)[P::R2], typename P::Ex* ex,
                                           const float2* stw) {
 #pragma unroll
   for (int u = 0; u < P::UB; ++u) {
@@ -172,7 +184,7 @@ __global__ __launch_bounds__(ZPencil<N>::T) void k_zinv(FieldPtrs in, FieldPtrs 
                                                          EpiArgs e) {
   using P = ZPencil<N>;
   constexpr int M = N / 2;
-  __shared__ __align__(16) float2 ex[P::LDS];
+  __shared__ __align__(16) typename P::Ex ex[P::LDS];
   __shared__ float2 stw_l[z_stw_len<N>()];
   // the fields' blocks alternate (field fastest), so fields written together by the
   // previous pass are read together
@@ -224,7 +236,7 @@ __global__ __launch_bounds__(ZHPencil<N>::T) void k_zinv_hess(FieldPtrs in, floa
                                                               float scale) {
   using P = ZHPencil<N>;
   constexpr int M = N / 2;
-  __shared__ __align__(16) float2 ex[P::LDS];
+  __shared__ __align__(16) typename P::Ex ex[P::LDS];
   __shared__ float2 stw_l[z_stw_len<N>()];
   const float2* stw = z_twiddles<N>(stw_l, tw);
   const long row0 = (long)blockIdx.x * P::NT;
@@ -269,12 +281,12 @@ __global__ __launch_bounds__(ZHPencil<N>::T) void k_zinv_hess(FieldPtrs in, floa
 // outside the sphere of complete shells (n_y^2 + k_z^2 > h^2 - h, h = n/2: shell h or
 // more) are left as they are, about a fifth of them; nothing reads those modes.
 template <int N, int B, int S>
-__global__ __launch_bounds__((Pencil<N, B, false>::T)) void k_col(FieldPtrs in, FieldPtrs out, long outer_stride,
+__global__ __launch_bounds__((ColPencil<N, B>::T)) void k_col(FieldPtrs in, FieldPtrs out, long outer_stride,
                                                                 long inner_stride, int ntiles_c,
                                                                 const float2* __restrict__ tw, int reverse,
                                                                 int rot, int ball) {
-  using P = Pencil<N, B, false>;
-  __shared__ __align__(16) float2 ex[P::LDS];
+  using P = ColPencil<N, B>;
+  __shared__ __align__(16) typename P::Ex ex[P::LDS];
   __shared__ float2 stw[N];
   const int f = blockIdx.y;
   const unsigned blk = reverse ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
@@ -318,8 +330,8 @@ __global__ __launch_bounds__((Pencil<N, B, false>::T)) void k_col_pair(const flo
                                                                      int ntiles_c, long ntiles,
                                                                      const float2* __restrict__ tw, int reverse,
                                                                      int rot) {
-  using P = Pencil<N, B, false>;
-  __shared__ __align__(16) float2 ex[P::LDS];
+  using P = PairPencil<N, B>;
+  __shared__ __align__(16) typename P::Ex ex[P::LDS];
   __shared__ float2 stw[N];
   constexpr bool ONE = col_pair_one_block<N>();
   long tile;
@@ -412,7 +424,7 @@ __global__ __launch_bounds__((Pencil<N, B, false>::T)) void k_xmul(const float2*
   using P = Pencil<N, B, false>;
   constexpr int H = N / 2;
   constexpr int NT = H / B;
-  __shared__ __align__(16) float2 ex[P::LDS];
+  __shared__ __align__(16) typename P::Ex ex[P::LDS];
   __shared__ float2 stw[N];
   int tc, y;
   xmul_tile<N>(NT, tc, y);
@@ -493,7 +505,7 @@ __global__ __launch_bounds__((Pencil<N, B, false>::T)) void k_xmul_adj(FieldPtrs
   using P = Pencil<N, B, false>;
   constexpr int H = N / 2;
   constexpr int NT = H / B;
-  __shared__ __align__(16) float2 ex[P::LDS];
+  __shared__ __align__(16) typename P::Ex ex[P::LDS];
   __shared__ float2 stw[N];
   load_twiddles(stw, tw, N);
   int tc, y;
