@@ -515,6 +515,21 @@ int lagrangian_finish(cola_plan p, const SortedState& src, const cola_particles*
                            [&] { return launch_kick_finish(lattice(p), c.f, src, g, finish_kick(p, row), st); }));
 }
 
+// Whether cola_run steps on the Lagrangian-order arrays (with the bins counted by the kick)
+// or on the tile-sorted copies.  The sorted form reads and writes the 52-byte state once a
+// step with the mesh in LDS; the other one moves 16 bytes to tile order and streams the
+// rest, which wins while the state stays in the 256 MB memory-side cache (np <= 128, 109
+// MB) and, up to np = 384, where a tile holds eight times the particles (nm = np) and
+// scatters as many.  Runs of a few launch-bound microseconds a kernel (np <= 32) keep the
+// sorted form, one launch a step shorter.  Sorted against Lagrangian, ms a run: 32/64 0.502
+// 0.510, 64/128 1.03 1.01, 96/192 2.31 2.21, 128/256 4.73 4.50, 192/384 15.8 16.0, 256/512
+// 36.6 37.4, 512/1024 303 314; nm = np: 32 0.90 0.77, 128 3.62 3.01, 256 16.7 15.9, 384
+// 55.3 54.5, 512 99 109.
+bool lagrangian_run(cola_plan p) {
+  const int np = p->cfg.np, nm = p->cfg.nm;
+  return nm == np ? np <= 384 : np > 32 && np <= 128;
+}
+
 int finish_impl(cola_plan p, const cola_particles* q, float* x_out, float* v_out, float* ws, hipStream_t st) {
   const bool ready = resident_ready(p, p->cfg.n_steps, q, ws);
   const int parity = ready ? p->res.parity : 0;
@@ -957,6 +972,16 @@ int cola_run(cola_plan p, const float* w, const cola_particles* q, float* x_out,
   if (!x_out || !v_out) return COLA_ERR_INVALID;
   float* ws = static_cast<float*>(ws_);
   hipStream_t st = (hipStream_t)stream;
+  if (lagrangian_run(p)) {
+    for (int i = 0; i < p->cfg.n_steps; ++i) {
+      hipError_t trc;
+      const long span = trace_open(p, 2, kStRunStep, st, trc);
+      COLA_HIP(trc);
+      COLA_TRY(lagrangian_step(p, i, soa(q), q, SortedState{}, i > 0, i & 1, true, ws, st));
+      COLA_HIP(trace_close(p, span, st));
+    }
+    return lagrangian_finish(p, soa(q), q, x_out, v_out, true, p->cfg.n_steps & 1, ws, st);
+  }
   const Lattice lat = lattice(p);
   const Bins& b = p->bins;
   const float mass = (float)std::pow((double)lat.ratio, 3);

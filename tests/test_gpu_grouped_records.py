@@ -1,6 +1,7 @@
 """The in-run gather writes each wave's records grouped by the tile they move to: whole
 runs and resident steps, which read that order, equal the steps that pack the caller's
-arrays afresh bit for bit.  Sizes: one tile along an axis, tiles with less than a wave,
+arrays afresh bit for bit.  Sizes on both sides of every line where a run steps on tile-sorted copies or
+on the Lagrangian-order arrays; one tile along an axis, tiles with less than a wave,
 with several batches and on the crowded list, and depths that make 256- and 512-thread
 tile blocks."""
 import pytest
@@ -13,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("np_side,nm,depth,box", [
-    (16, 16, 16, 20.0), (24, 48, 8, 10.0), (32, 32, 32, 5.0), (48, 192, 64, 60.0), (64, 64, 64, 8.0), (96, 96, 32, 30.0)])
+    (16, 16, 16, 20.0), (24, 48, 8, 10.0), (32, 32, 32, 5.0), (48, 192, 64, 60.0), (64, 64, 64, 8.0), (96, 96, 32, 30.0),
+    (16, 32, 32, 4.0), (16, 48, 16, 20.0), (32, 64, 64, 6.0), (32, 128, 8, 30.0), (192, 384, 32, 40.0), (384, 768, 64, 80.0)])
 def test_grouped_records_equal_fresh_packing(np_side, nm, depth, box):
     announce(f"grouped records {np_side}/{nm} depth {depth} box {box}")
     cfg = cola.Config(np=np_side, nm=nm, box=box, n_steps=4)
