@@ -196,7 +196,7 @@ struct KickArgs {
 enum GatherMode : int {
   kGatherKickDrift = 1,     // v += alpha (F - t2d1 s1 - t2d2 s2); s += beta v + dd1 s1 + dd2 s2, written
                             // packed in this step's tile order and binned for the next step
-  kGatherFinish = 2,        // the kick only, written packed for launch_unsort (x, L+)
+  kGatherFinish = 2,        // the kick only, written in Lagrangian order for launch_unsort (x, L+)
 };
 struct GatherArgs {
   const float* g0;
@@ -230,12 +230,12 @@ struct SortedState {
 // Gather + kick over the tile lists bb.idx (slots of src).  kGatherKickDrift writes
 // the kicked and drifted record of list position j to slot j of the packed dst
 // (ordered by this step's tiles) and bins it for the next step (bb.count_next,
-// bb.key_rank by dst slot); kGatherFinish writes s and the kicked v of list position
-// j as float4 j of dst.s (s.x s.y s.z v.x) and float2 j of dst.s + 4n (v.y v.z), and
-// sets dst.lag[Lagrangian index] = j, for launch_unsort.
+// bb.key_rank by dst slot); kGatherFinish writes s and the kicked v in Lagrangian order, as
+// float4 p of dst.s (s.x s.y s.z v.x) and float2 p of dst.s + 4n (v.y v.z), for
+// launch_unsort.
 hipError_t launch_gather_sorted(Lattice lat, Bins b, SortedState src, SortedState dst, BinBuffers bb, int mode,
                                 GatherArgs a, KickArgs k, hipStream_t st);
-// Lagrangian order from a kGatherFinish output w: a.s, a.v take s and v; a.out_a
+// The caller's arrays from a kGatherFinish output w: a.s, a.v take s and v; a.out_a
 // x = (q + s) mod L (k.box); a.out_b v_phys = v + k.td1 a.s1 + k.td2 a.s2, the L+ of
 // the closing step (a.s1, a.s2 the caller's arrays).
 hipError_t launch_unsort(Lattice lat, SortedState w, GatherArgs a, KickArgs k, hipStream_t st);

@@ -1062,12 +1062,10 @@ __global__ __launch_bounds__(TileDims<TZ>::TT) void k_gather_sorted(Lattice lat,
         vf[d] = v;
       }
       if constexpr (MODE == kGatherFinish) {
-        // finish: s and the kicked v, in this step's tile order, as a float4 plane
-        // (s.x s.y s.z v.x) and a float2 plane (v.y v.z), and the slot of every
-        // Lagrangian index in dst.lag, for k_unsort (which forms x and v_phys)
-        reinterpret_cast<float4*>(dst.s)[j] = make_float4(r.s[0], r.s[1], r.s[2], vf[0]);
-        reinterpret_cast<float2*>(dst.s + 4 * n)[j] = make_float2(vf[1], vf[2]);
-        dst.lag[r.lag] = j;
+        // finish: s and the kicked v to Lagrangian order, as a float4 plane (s.x s.y s.z v.x)
+        // and a float2 plane (v.y v.z), for k_unsort (which forms x and v_phys)
+        reinterpret_cast<float4*>(dst.s)[r.lag] = make_float4(r.s[0], r.s[1], r.s[2], vf[0]);
+        reinterpret_cast<float2*>(dst.s + 4 * n)[r.lag] = make_float2(vf[1], vf[2]);
       }
     }
     if constexpr (BINS) {
@@ -1306,29 +1304,12 @@ hipError_t launch_gather_sorted(Lattice lat, Bins b, SortedState src, SortedStat
   return hipGetLastError();
 }
 
-// Lagrangian order from the finish output: particle p takes s and v from slot inv[p]
-// of the tile-ordered finish copy, then L+(a_n) (eq. Lops): v_phys = v + T[D1] s1 +
-// T[D2] s2 (k.td1, k.td2; s1, s2 from the caller's arrays, read in order) and
-// x = (q + s) mod L.  Only 24 bytes per particle are read out of order.  A block
-// covers a 4 x 4 x 16 block of the Lagrangian grid (when np allows), whose particles
-// sit in a few neighbouring tiles, so its scattered reads stay local; its writes are
-// runs of 16 consecutive elements.
-// Lagrangian index of this thread in the unsort-order walks: a block takes a 4 x 4 x 16
-// block of the Lagrangian grid (when np allows), whose particles sit in a few
-// neighbouring tiles, so its out-of-order reads stay local and its writes are runs of
-// 16 consecutive elements.
-__device__ __forceinline__ long unsort_index(const Lattice& lat) {
-  const int np = lat.np;
-  if (np % 16 == 0) {
-    const int nbk = np / 16, nbj = np / 4;
-    const int b = blockIdx.x;
-    const int bk = b % nbk, bj = (b / nbk) % nbj, bi = b / (nbk * nbj);
-    const int t = threadIdx.x;
-    return ((long)(4 * bi + t / 64) * np + 4 * bj + (t / 16) % 4) * np + 16 * bk + t % 16;
-  }
-  return (long)blockIdx.x * kPartThreads + threadIdx.x;
-}
-
+// The closing gather's output (s and v of every particle in Lagrangian order) into the
+// caller's arrays, with L+(a_n) (eq. Lops): v_phys = v + T[D1] s1 + T[D2] s2 (k.td1, k.td2;
+// s1, s2 from the caller's arrays) and x = (q + s) mod L; every access in order.  The gather
+// scatters 24 bytes a particle so that this pass need not collect them through a
+// permutation: 256^3 particles, gather 0.93 -> 1.13 ms, this 0.61 -> 0.28 (512^3: 6.9 -> 8.3
+// and 4.8 -> 2.25; one 32-byte record a particle instead of two planes: 0.30 here).
 // Component d of the outputs of particle p: x = (q + s) mod L and v_phys (eq. Lops).
 __device__ __forceinline__ void closing_outputs(const Lattice& lat, const GatherArgs& g, const KickArgs& k, long p,
                                                 int d, int li, float s, float v, float s1, float s2) {
@@ -1341,11 +1322,10 @@ __device__ __forceinline__ void closing_outputs(const Lattice& lat, const Gather
 
 __global__ __launch_bounds__(kPartThreads) void k_unsort(Lattice lat, SortedState w, GatherArgs g, KickArgs k) {
   const long n = lat.npart;
-  const long p = unsort_index(lat);
+  const long p = (long)blockIdx.x * kPartThreads + threadIdx.x;
   if (p >= n) return;
-  const long j = w.lag[p];
-  const float4 a = reinterpret_cast<const float4*>(w.s)[j];
-  const float2 b = reinterpret_cast<const float2*>(w.s + 4 * n)[j];
+  const float4 a = reinterpret_cast<const float4*>(w.s)[p];
+  const float2 b = reinterpret_cast<const float2*>(w.s + 4 * n)[p];
   const float sv[3] = {a.x, a.y, a.z}, vv[3] = {a.w, b.x, b.y};
   int li[3];
   lag_index(lat, (unsigned)p, li);
