@@ -793,9 +793,9 @@ __global__ __launch_bounds__((deposit_threads<TZ, NW>())) void k_deposit_tiles(L
 }
 
 // ---------------------------------------------------------------------------------
-// Force gather, tile by tile: the PM force at every particle of the caller's
-// Lagrangian-order displacements (cola_pm_force).  The kick and drift gathers are
-// k_gather_sorted's.
+// Force gather, tile by tile: the PM force at every particle of Lagrangian-order
+// displacements (cola_pm_force, and the steps that stream their kick in that order).  The
+// kick and drift of tile-sorted runs are k_gather_sorted's.
 // ---------------------------------------------------------------------------------
 // The particle at list position i: slot through idx into the SoA displacements s, or with
 // pos (tile-sorted positions) directly.
