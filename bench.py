@@ -570,9 +570,9 @@ def main() -> int:
     pm_step_ms = steps_rec[0] / steps_rec[1]
 
     # the same step through the public cola_step call, median over steps 1..n-1: plain
-    # (the caller's Lagrangian-order arrays binned and packed from scratch each call)
-    # and with resident steps (each call continues from the sorted state the previous
-    # one left in the workspace)
+    # (the caller's Lagrangian-order arrays binned from scratch each call) and with
+    # resident steps (each call continues from the particles and bins the previous one
+    # left in the workspace)
     def public_steps(resident):
         plan.set_resident_steps(resident)
         plan.init_2lpt(w, p, ws)
@@ -653,7 +653,7 @@ def main() -> int:
                         "ms": res_step_ms, "particle_steps_per_s": np_side**3 / (res_step_ms * 1e-3),
                         "hbm_frac": b_alg / (res_step_ms * 1e-3) / (HBM_PEAK_GBS * 1e9),
                         "timed": "the public cola_step call with resident steps on (each call continues from the "
-                                 "tile-sorted state the previous call left in the workspace and writes s, v to the "
+                                 "particles and bins the previous call left in the workspace and writes s, v to the "
                                  "caller's arrays), HIP events around each call, median over steps 1.."
                                  f"{cfg.n_steps - 1} after cola_init_2lpt",
                         "stages_ms_per_call": res_stages}},

@@ -111,7 +111,8 @@ int cola_plan_destroy(cola_plan plan);
 /* Bytes of workspace every call below needs: four nm^3 float meshes, the
  * per-step particle binning buffers (12 bytes per particle, three int arrays of
  * one entry per 8x8xtz tile, the halo faces of every tile) and two tile-sorted
- * copies of the particle state used by cola_run (104 bytes per particle). */
+ * copies of the particle state (104 bytes per particle) used by cola_run and, for sorted
+ * positions and forces, by the calls on the caller's arrays. */
 int cola_workspace_bytes(cola_plan plan, size_t *bytes);
 
 /* Host copy of the per-step scalars (FP64).  out receives n = 13 * (n_steps + 1)
@@ -206,10 +207,10 @@ int cola_plan_set_resident_steps(cola_plan plan, int32_t on);
 int cola_finish(cola_plan plan, const cola_particles *p, float *x_out, float *v_out, void *ws, void *stream);
 
 /* Whole run: cola_init_2lpt, then the n_steps COLA steps and the closing kick of
- * cola_step / cola_finish.  Internally the particle state is kept in workspace
- * copies sorted by mesh tile between force evaluations, with the same arithmetic:
- * the results equal those of the step-by-step calls bit for bit (the mass deposit
- * sums 64-bit fixed point, independent of particle order).  On return p holds the
+ * cola_step / cola_finish.  Depending on the sizes the particle state is kept in
+ * workspace copies sorted by mesh tile between force evaluations, with the same
+ * arithmetic: the results equal those of the step-by-step calls bit for bit (the mass
+ * deposit sums 64-bit fixed point, independent of particle order).  On return p holds the
  * final s, v_res (in Lagrangian order) and the unchanged s1, s2. */
 int cola_run(cola_plan plan, const float *w, const cola_particles *p, float *x_out, float *v_out, void *ws,
              void *stream);

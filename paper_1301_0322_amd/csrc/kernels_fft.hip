@@ -862,7 +862,7 @@ __global__ __launch_bounds__(kShellThreads) void k_shell_sums(int n, const float
     const int sh = shell_of(x * x + y * y + kz * kz);
     if (sh < 1 || sh >= h) continue;
     // r bit 0: -x, bit 1: -y, bit 2: exchanged.  A row that repeats another (x or y is 0,
-    // or x = y) is loaded with weight 0, so that no load waits behind a branch.
+    // or x = y) is loaded and left out, so that no load waits behind a branch.
     float2 va[8], vb[8];
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
@@ -876,11 +876,13 @@ __global__ __launch_bounds__(kShellThreads) void k_shell_sums(int n, const float
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
       const bool once = !((r & 1) && x == 0) && !((r & 2) && y == 0) && !((r & 4) && x == y);
-      const double u = once ? 1.0 : 0.0;
-      aa += u * ((double)va[r].x * va[r].x + (double)va[r].y * va[r].y);
+      const double ra = (double)va[r].x * va[r].x + (double)va[r].y * va[r].y;
+      aa += once ? ra : 0.0;
       if (b) {
-        bb += u * ((double)vb[r].x * vb[r].x + (double)vb[r].y * vb[r].y);
-        ab += u * ((double)va[r].x * vb[r].x + (double)va[r].y * vb[r].y);
+        const double rb = (double)vb[r].x * vb[r].x + (double)vb[r].y * vb[r].y;
+        const double rab = (double)va[r].x * vb[r].x + (double)va[r].y * vb[r].y;
+        bb += once ? rb : 0.0;
+        ab += once ? rab : 0.0;
       }
       rows += once;
     }
