@@ -286,6 +286,17 @@ int cola_plan_set_fft_rotation(cola_plan plan, int32_t on);
  * Host-only. */
 int cola_plan_get_fft_rotation(cola_plan plan, int32_t *rows);
 
+/* Form of the steps inside cola_run (a tuning knob; results are identical bit for bit
+ * either way).  form = 0 keeps the particle state in two workspace copies sorted by mesh
+ * tile, form = 1 steps on the caller's Lagrangian-order arrays with only the positions
+ * sorted, form = -1 restores the built-in choice by np and nm; other values give
+ * COLA_ERR_INVALID.  cola_step, cola_finish and cola_run_checkpointed always use
+ * Lagrangian-order steps.  Host-only. */
+int cola_plan_set_run_form(cola_plan plan, int32_t form);
+/* The form cola_run takes with this plan: 0 tile-sorted copies, 1 Lagrangian order.
+ * Host-only. */
+int cola_plan_get_run_form(cola_plan plan, int32_t *form);
+
 /* Current tuning: y-pass and x-pass tile widths (0 = built-in default) and bin
  * depth.  Host-only. */
 int cola_plan_get_tuning(cola_plan plan, int32_t *y_width, int32_t *x_width, int32_t *bin_depth);

@@ -66,6 +66,8 @@ _PROTOS = {
     "cola_plan_set_fft_rotation": (ctypes.c_int, [_VP, ctypes.c_int32]),
     "cola_plan_set_resident_steps": (ctypes.c_int, [_VP, ctypes.c_int32]),
     "cola_plan_get_fft_rotation": (ctypes.c_int, [_VP, ctypes.POINTER(ctypes.c_int32)]),
+    "cola_plan_set_run_form": (ctypes.c_int, [_VP, ctypes.c_int32]),
+    "cola_plan_get_run_form": (ctypes.c_int, [_VP, ctypes.POINTER(ctypes.c_int32)]),
     "cola_plan_get_tuning": (ctypes.c_int, [_VP, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32),
                                             ctypes.POINTER(ctypes.c_int32)]),
     "cola_autotune": (ctypes.c_int, [_VP, ctypes.POINTER(ColaParticles), _VP, ctypes.c_size_t, _VP,
@@ -347,6 +349,17 @@ class Plan:
         r = ctypes.c_int32()
         _check("cola_plan_get_fft_rotation", lib().cola_plan_get_fft_rotation(self._c, ctypes.byref(r)))
         return r.value
+
+    def set_run_form(self, form: int):
+        """Form of the steps inside run(): 0 tile-sorted copies of the state, 1
+        Lagrangian-order arrays, -1 the default by size.  Results are identical."""
+        _check("cola_plan_set_run_form", lib().cola_plan_set_run_form(self._c, form))
+
+    def get_run_form(self) -> int:
+        """The form run() takes: 0 tile-sorted copies, 1 Lagrangian-order arrays."""
+        form = ctypes.c_int32()
+        _check("cola_plan_get_run_form", lib().cola_plan_get_run_form(self._c, ctypes.byref(form)))
+        return form.value
 
     def get_tuning(self):
         y, x, tz = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()

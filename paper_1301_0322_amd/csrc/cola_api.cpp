@@ -30,6 +30,7 @@ struct cola_plan_s {
   Bins bins;                      // Eulerian tiles of the force mesh
   int fft_width[2] = {0, 0};      // columns per tile of the mesh-size y passes and x pass (0: default)
   int fft_rot = -1;               // rotate the mesh-size half spectrum between y and x: 1 / 0 (-1: default)
+  int run_form = -1;              // form of cola_run's steps: 0 tile-sorted copies, 1 Lagrangian order (-1: by size)
   // resident steps (cola_plan_set_resident_steps): the copy and bins the last one left in
   // its workspace, and the workspace generation of the current call
   int resident = 0;
@@ -526,6 +527,7 @@ int lagrangian_finish(cola_plan p, const SortedState& src, const cola_particles*
 // 36.6 37.4, 512/1024 303 314; nm = np: 32 0.90 0.77, 128 3.62 3.01, 256 16.7 15.9, 384
 // 55.3 54.5, 512 99 109.
 bool lagrangian_run(cola_plan p) {
+  if (p->run_form >= 0) return p->run_form == 1;
   const int np = p->cfg.np, nm = p->cfg.nm;
   return nm == np ? np <= 384 : np > 32 && np <= 128;
 }
@@ -1137,6 +1139,18 @@ int cola_plan_set_fft_rotation(cola_plan p, int32_t on) {
 int cola_plan_get_fft_rotation(cola_plan p, int32_t* rot) {
   if (!p || !rot) return COLA_ERR_INVALID;
   *rot = rot_for(p, p->cfg.nm);
+  return COLA_OK;
+}
+
+int cola_plan_set_run_form(cola_plan p, int32_t form) {
+  if (!p || form < -1 || form > 1) return COLA_ERR_INVALID;
+  p->run_form = form;
+  return COLA_OK;
+}
+
+int cola_plan_get_run_form(cola_plan p, int32_t* form) {
+  if (!p || !form) return COLA_ERR_INVALID;
+  *form = lagrangian_run(p) ? 1 : 0;
   return COLA_OK;
 }
 
