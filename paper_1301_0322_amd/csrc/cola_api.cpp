@@ -517,19 +517,29 @@ int lagrangian_finish(cola_plan p, const SortedState& src, const cola_particles*
 }
 
 // Whether cola_run steps on the Lagrangian-order arrays (with the bins counted by the kick)
-// or on the tile-sorted copies.  The sorted form reads and writes the 52-byte state once a
-// step with the mesh in LDS; the other one moves 16 bytes to tile order and streams the
-// rest, which wins while the state stays in the 256 MB memory-side cache (np <= 128, 109
-// MB) and, up to np = 384, where a tile holds eight times the particles (nm = np) and
-// scatters as many.  Runs of a few launch-bound microseconds a kernel (np <= 32) keep the
-// sorted form, one launch a step shorter.  Sorted against Lagrangian, ms a run: 32/64 0.502
-// 0.510, 64/128 1.03 1.01, 96/192 2.31 2.21, 128/256 4.73 4.50, 192/384 15.8 16.0, 256/512
-// 36.6 37.4, 512/1024 303 314; nm = np: 32 0.90 0.77, 128 3.62 3.01, 256 16.7 15.9, 384
-// 55.3 54.5, 512 99 109.
+// or on the tile-sorted copies.  The sorted form moves 152 bytes a particle and step (scan
+// lists, deposit, gather), most of them as 52-byte records read out of order; the other one
+// moves 180, but only 16-byte positions and forces out of order.  So the second wins where
+// the order counts, in small sets and in crowded ones (the finer the particle spacing, the
+// more crowded a run gets), and the first in large, even ones.  Time of the Lagrangian run
+// over the sorted one, 10 steps to z = 0, at particle spacings of 0.2, 0.5 (np = nm: 0.4), 1
+// and 2 Mpc/h (two runs of one form differ by 0.2-0.5%, below np = 48 by up to 3%):
+//   np = nm:  64  .78 .80 .84 .89    128  .71 .79 .88 .96    192  .78 .83 1.00 1.03
+//            256  .90 .99 1.06 1.07  384  1.02 1.06 1.10 1.10
+//   nm = 2 np: 32 .86 .95 .96 .98 (3.1 Mpc/h: 1.01)  48  .80 .90 .96 1.02   64  .85 .87 .94 1.00
+//             96  .86 .92 1.00 1.01  128  .81 .94 .96 .99    192  .97 1.01 1.02 1.02
+//            256  1.01 1.04 1.05 1.04
+//   nm = 3 np: 32 .93 .98 1.01 1.03   64  .87 .97 1.00 1.01  128  .98 1.00 1.00 1.00
+//            256  1.01 (0.4 Mpc/h)
+//   nm = 4 np: 32 .97 .97 1.00 1.00   48  .98 .96 1.01 1.01   64  .96 .96 .97 .98
+//             96  .99 1.00 .99 .99   128  1.00 1.01 1.00 1.00   192  1.01 (0.5 Mpc/h)
+// On finer meshes np = 16 to 32 stays with the sorted form, one launch a step shorter: even
+// sets of these sizes (3 to 6 Mpc/h) lose 1 to 6% with the other one.
 bool lagrangian_run(cola_plan p) {
   if (p->run_form >= 0) return p->run_form == 1;
   const int np = p->cfg.np, nm = p->cfg.nm;
-  return nm == np ? np <= 384 : np > 32 && np <= 128;
+  if (nm == np) return np <= 192 || (np == 256 && p->cfg.box < 0.4 * np);
+  return np > 32 && np <= 128;
 }
 
 int finish_impl(cola_plan p, const cola_particles* q, float* x_out, float* v_out, float* ws, hipStream_t st) {

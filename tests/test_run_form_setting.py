@@ -18,3 +18,13 @@ def test_run_form_setting():
         assert p.get_run_form() == default
     lib = cola.lib()
     assert lib.cola_plan_set_run_form(None, 0) == -1 and lib.cola_plan_get_run_form(None, None) == -1
+
+
+# sizes where the measured times of the two forms differ by 3% and more
+@pytest.mark.parametrize("np_side,nm,spacing,form", [
+    (32, 32, 1.0, 1), (128, 128, 0.5, 1), (192, 192, 0.3, 1), (256, 256, 0.2, 1), (256, 256, 1.0, 0),
+    (256, 256, 2.0, 0), (384, 384, 0.5, 0), (384, 384, 2.0, 0), (512, 512, 0.3, 0), (32, 96, 2.0, 0),
+    (48, 96, 0.5, 1), (64, 192, 0.2, 1), (64, 256, 0.5, 1), (128, 256, 0.8, 1), (256, 512, 0.5, 0)])
+def test_default_form_is_the_faster_one(np_side, nm, spacing, form):
+    with cola.Plan(cola.Config(np=np_side, nm=nm, box=spacing * np_side)) as p:
+        assert p.get_run_form() == form
