@@ -119,16 +119,21 @@ __device__ __forceinline__ const float2* z_twiddles(float2* stw, const float2* _
 // where Z is the length-M = N/2 DFT of z[m] = x[2m] + i x[2m+1].  Z[M-k] sits in the
 // partner lane of the same wave (Pencil::partner).
 // ---------------------------------------------------------------------------------
-// blockIdx.y selects the field.
-template <int N>
-__global__ __launch_bounds__(ZPencil<N>::T) void k_zfwd(FieldPtrs in, FieldPtrs out, const float2* __restrict__ tw) {
+// F = FieldPtrs: blockIdx.y selects the field.  F = float2*: one field, whose pointers come
+// with the other arguments (picked from the list they cost a launch 0.2 to 0.3 us, 0.9% of
+// a 192^3 transform).
+__device__ __forceinline__ float2* field_of(const FieldPtrs& f) { return f.p[blockIdx.y]; }
+__device__ __forceinline__ float2* field_of(float2* f) { return f; }
+
+template <int N, class F>
+__global__ __launch_bounds__(ZPencil<N>::T) void k_zfwd(F in, F out, const float2* __restrict__ tw) {
   using P = ZPencil<N>;
   constexpr int M = N / 2;
   __shared__ __align__(16) typename P::Ex ex[P::LDS];
   __shared__ float2 stw_l[z_stw_len<N>()];
   const long row0 = (long)blockIdx.x * P::NT;
   float2 a[P::R2];
-  P::load_a(a, in.p[blockIdx.y] + row0 * M, M);
+  P::load_a(a, field_of(in) + row0 * M, M);
   const float2* stw = z_twiddles<N>(stw_l, tw);
   __syncthreads();
   float2 q[P::UB][P::R1];
@@ -149,7 +154,7 @@ __global__ __launch_bounds__(ZPencil<N>::T) void k_zfwd(FieldPtrs in, FieldPtrs 
       q[u][j1] = c_add(s, mul_si<-1>(c_mul(stw[k], d)));
     }
   }
-  P::store_b(q, out.p[blockIdx.y] + row0 * M, M);
+  P::store_b(q, field_of(out) + row0 * M, M);
 }
 
 // ---------------------------------------------------------------------------------
@@ -584,7 +589,11 @@ template <int N>
 static hipError_t zfwd_t(FieldPtrs in, FieldPtrs out, int nf, long nrows, const float2* tw, hipStream_t st) {
   using P = ZPencil<N>;
   if (nrows % P::NT || nf < 1 || nf > kMaxFields) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_zfwd<N>, dim3((unsigned)(nrows / P::NT), nf), dim3(P::T), 0, st, in, out, tw);
+  const dim3 grid((unsigned)(nrows / P::NT), nf);
+  if (nf == 1)
+    hipLaunchKernelGGL((k_zfwd<N, float2*>), grid, dim3(P::T), 0, st, in.p[0], out.p[0], tw);
+  else
+    hipLaunchKernelGGL((k_zfwd<N, FieldPtrs>), grid, dim3(P::T), 0, st, in, out, tw);
   return hipGetLastError();
 }
 
