@@ -67,17 +67,23 @@ constexpr int col_width_default() {
   return col_ok<N, 16>() ? 16 : col_ok<N, 8>() ? 8 : 4;
 }
 
-// Tiles of the single and paired column passes.  At 384 and 1024 the exchange (52 and
-// 135 KB) leaves two blocks and one to a CU; split it leaves five and two, and those passes
-// do not need the registers that would cap them lower.  384 (steps of 192^3
+// Tiles of the single and paired column passes.  At 384 and 1024 the exchange of a 16-wide
+// tile (52 and 135 KB) leaves two blocks and one to a CU; split it leaves five and two, and
+// those passes do not need the registers that would cap them lower.  384 (steps of 192^3
 // particles): pair 0.197 -> 0.159 ms, inverse 0.110 -> 0.098, forward 0.076 -> 0.073.  1024:
-// forward 1.78 -> 1.66 ms, inverse 1.81 -> 1.74.  At 256, 512 and 768 it measured no gain,
-// nor in the x passes, whose registers set their residency (384: 0.215 -> 0.232 ms), nor in
-// the one-block pair at 1024.
+// forward 1.78 -> 1.66 ms, inverse 1.81 -> 1.74.  Narrower tiles have the residency without
+// it and pay for its barriers: a force on 384^3 cells with 8-wide tiles takes 1.514 ms
+// unsplit and 1.533 split, on 1024^3 32.0 and 32.4; only 4-wide tiles at 1024 gain (46.1
+// against 45.8).  At 256 and 768 the split measured no gain, nor in the x passes, whose
+// registers set their residency (384: 0.215 -> 0.232 ms), nor in the one-block pair at 1024.
+// A length-512 column has more than one second-stage transform a thread and is exchanged in
+// chunks, which is not combined with the split.
 template <int N, int B>
-using ColPencil = Pencil<N, B, false, N == 384 || N == 1024>;
+constexpr bool split_col() { return (N == 384 && B == 16) || (N == 1024 && B != 8); }
 template <int N, int B>
-using PairPencil = Pencil<N, B, false, N == 384>;
+using ColPencil = Pencil<N, B, false, split_col<N, B>()>;
+template <int N, int B>
+using PairPencil = Pencil<N, B, false, N == 384 && split_col<N, B>()>;
 
 // Stored row of logical row y of x-plane x in a rotated half spectrum.
 template <int N>
