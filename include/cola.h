@@ -186,9 +186,11 @@ int cola_pm_force(cola_plan plan, const float *s, double a, float *acc, void *ws
  * starts from the state that call left in ws. */
 int cola_step(cola_plan plan, int32_t i, const cola_particles *p, void *ws, void *stream);
 
-/* Resident steps (off by default).  With on = 1, cola_step leaves in ws a copy of the
- * updated particle arrays and their tile bins for the next step, and still writes s and v
- * to the caller's arrays.  The next cola_step (or cola_finish) of this plan continues from
+/* Resident steps (off by default), for small particle sets, where they save a pass and two
+ * launches a step (1 to 5%).  With on = 1 and np <= 128 (np <= 96 when nm = np), cola_step
+ * leaves in ws a copy of the updated particle arrays and their tile bins for the next step,
+ * and still writes s and v to the caller's arrays.  Larger sets would lose by the copy:
+ * their steps leave nothing behind and equal those with on = 0.  The next cola_step (or cola_finish) of this plan continues from
  * them, skipping the binning of the caller's arrays, when it is called with step index
  * i + 1 (n_steps for cola_finish), the same particle arrays and the same ws, and no
  * other call of this library has used ws in between; in every other case it starts

@@ -434,6 +434,19 @@ KickArgs finish_kick(cola_plan p, const StepRow& row) {
 // arrays and workspace, the next step index, and no other call on that workspace since)
 // starts from them; otherwise it bins and reads the caller's arrays.  s and v are written
 // to the caller's arrays in either case, which are therefore current after every step.
+//
+// Whether a resident step leaves anything behind.  The copy writes 24 bytes a particle at
+// every step and the counting kick saves 12 bytes, two launches and a pass; small sets gain
+// by it and large ones lose, most where a tile holds most particles (np = nm).  A resident
+// step over a plain one at particle spacings of 0.3 and 1.5 Mpc/h (ms a plain step at 0.3):
+//   np = nm:  32 .97 .96 (0.069)  64 1.00 .99 (0.15)  96 .99 .98 (0.21)  128 1.00 1.06 (0.34)
+//            192 1.00 1.06 (0.97)  256 1.02 1.04 (1.51)  512 1.04 (9.9)
+//   nm = 2 np: 32 .97 .96 (0.060)  64 1.00 .97 (0.15)  96 .99 .98 (0.26)  128 .98 1.01 (0.44)
+//            192 .99 1.01 (1.59)  256 1.00 1.02 (3.43)  384 1.00 1.02 (12.5)  512 1.00 1.01 (29.3)
+//   nm = 3 np: 32 .96 .96  64 1.00 .99  128 .99 .99 (1.18)  256 1.00 1.00 (10.2)
+//   nm = 4 np: 96 1.00 1.00  128 1.00 1.00 (2.51)  192 1.00 1.00  256 .99 1.00 (22.4)
+bool resident_pays(cola_plan p) { return p->cfg.np <= (p->cfg.nm > p->cfg.np ? 128 : 96); }
+
 bool resident_ready(cola_plan p, int i, const cola_particles* q, const float* ws) {
   const auto& r = p->res;
   return r.valid && r.ws == ws && r.s == q->s && r.v == q->v && r.s1 == q->s1 && r.s2 == q->s2 && r.next == i &&
@@ -480,6 +493,7 @@ int step_impl(cola_plan p, int i, const cola_particles* q, float* ws, hipStream_
 }
 
 int resident_step(cola_plan p, int i, const cola_particles* q, float* ws, hipStream_t st) {
+  if (!resident_pays(p)) return step_impl(p, i, q, ws, st);
   const bool ready = resident_ready(p, i, q, ws);
   const int parity = ready ? p->res.parity : 0;
   p->res.valid = false;
