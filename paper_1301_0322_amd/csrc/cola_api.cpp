@@ -968,7 +968,16 @@ int cola_pm_force(cola_plan p, const float* s, double a, float* acc, void* ws_, 
   if (!s || !acc || !(a > 0)) return COLA_ERR_INVALID;
   hipStream_t st = (hipStream_t)stream;
   float* ws = static_cast<float*>(ws_);
-  const BinBuffers bb = pos_buffers(p, ws);
+  // Sorted positions are written 16 bytes at a time out of order and then read in order
+  // three times over; the lists write 4 bytes and fetch 12 out of order twice.  The first
+  // wins where the fetches are scattered or the set is small, the second in large even sets.
+  // Sorted against lists at displacements of 0.3, 1 (a tenth of the particles collapsed)
+  // and 8 particle spacings, ms: 64/64 0.061 0.062, 0.244 0.274, 0.125 0.136; 256/512 2.87
+  // 2.81, 2.96 2.93, 3.13 3.23; 384/384 2.64 2.51, 2.73 2.59, 3.37 3.55; 512/1024 24.3 23.8,
+  // 24.6 24.1, 25.6 26.1; 512/512 6.17 5.76, 6.37 5.92, 6.99 7.10: only there the lists win
+  // by more than they lose on the other side.
+  const bool lists = p->cfg.np >= 512 && p->cfg.nm == p->cfg.np;
+  const BinBuffers bb = lists ? bin_buffers(p, ws) : pos_buffers(p, ws);
   COLA_TRY(pm_mesh(p, s, a, ws, bb, st));
   GatherArgs g = gather_args(p, ws);
   g.s = const_cast<float*>(s);
