@@ -304,13 +304,15 @@ int cola_plan_get_run_form(cola_plan plan, int32_t *form);
 int cola_plan_get_tuning(cola_plan plan, int32_t *y_width, int32_t *x_width, int32_t *bin_depth);
 
 /* Autotuner: picks the FFT tile widths and the bin depth of the plan by timing one
- * PM force evaluation of the particles p (device) for every valid combination
- * (HIP events on stream, best of two repetitions) and keeps the fastest.  With
+ * PM force evaluation of the particles p (device), as cola_step runs it, for every valid
+ * combination (HIP events on stream, best of two repetitions) and keeps the fastest.  With
  * cache_path (a text file, may be NULL) a previous choice for the same
  * (np, nm, GPU architecture) is reused without measuring, and a new choice is
  * appended.  *used_cache (nullable) reports whether the cache answered.  ws holds
  * ws_bytes bytes (cola_tuning_workspace_bytes() lets every depth be tried; depths
- * whose binning buffers would not fit are skipped).  Call cola_workspace_bytes
+ * whose binning buffers would not fit are skipped, and without room for the sorted
+ * positions and forces, 32 bytes a particle, the evaluation is timed up to the force
+ * meshes only, through tile lists).  Call cola_workspace_bytes
  * again afterwards.  This call synchronises stream.
  * Results of the tuned plan equal the default's bit for bit: no tuning knob changes
  * the arithmetic (tile widths set how many columns a block transforms, the bin depth

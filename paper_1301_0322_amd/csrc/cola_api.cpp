@@ -1200,7 +1200,9 @@ int cola_tuning_workspace_bytes(cola_plan p, size_t* bytes) {
   size_t worst = 0;
   for (int tz : {8, 16, 32, 64})
     if (p->cfg.nm % tz == 0) worst = std::max(worst, bin_workspace_bytes(cube(p->cfg.np), make_bins(p->cfg.nm, tz)));
-  *bytes = mesh_floats(p) * sizeof(float) + worst;
+  // binning buffers, then sorted positions and forces (a float4 a particle each) from the
+  // next 16-byte boundary
+  *bytes = mesh_floats(p) * sizeof(float) + worst + 16 + 2 * sizeof(float4) * (size_t)cube(p->cfg.np);
   return COLA_OK;
 }
 
@@ -1241,8 +1243,10 @@ int cola_autotune(cola_plan p, const cola_particles* q, void* ws_, size_t ws_byt
       std::fclose(fh);
     }
   }
-  // Measure every valid combination on the PM force of the given particles; tile
-  // depths whose binning buffers would not fit the given workspace are skipped.
+  // Measure every valid combination on the PM force of the given particles, by the path of
+  // a step (lagrangian_force) where the workspace holds its positions and forces too, else
+  // up to the force meshes through tile lists; tile depths whose binning buffers would not
+  // fit the given workspace are skipped.
   const bool was_tracing = p->trace;
   if (ws_bytes < mesh_floats(p) * sizeof(float)) return COLA_ERR_INVALID;
   const size_t bin_cap = ws_bytes - mesh_floats(p) * sizeof(float);
@@ -1261,6 +1265,18 @@ int cola_autotune(cola_plan p, const cola_particles* q, void* ws_, size_t ws_byt
     if (p->cfg.nm % tz) continue;
     if (bin_workspace_bytes(cube(p->cfg.np), make_bins(p->cfg.nm, tz)) > bin_cap) continue;
     p->bins = make_bins(p->cfg.nm, tz);
+    BinBuffers bb = bin_buffers(p, ws);
+    float4* force = nullptr;
+    const size_t head = mesh_floats(p) * sizeof(float) + bin_workspace_bytes(cube(p->cfg.np), p->bins);
+    const size_t at = head + (16 - (reinterpret_cast<uintptr_t>(ws) + head) % 16) % 16;
+    if (at + 2 * sizeof(float4) * (size_t)cube(p->cfg.np) <= ws_bytes) {
+      bb.pos = reinterpret_cast<float4*>(reinterpret_cast<char*>(ws) + at);
+      force = bb.pos + cube(p->cfg.np);
+    }
+    auto evaluate = [&] {
+      return force ? lagrangian_force(p, q->s, p->table[0].a, ws, bb, false, false, st, force)
+                   : pm_mesh(p, q->s, p->table[0].a, ws, bb, st);
+    };
     for (int y : widths) {
       if (!fft_width_supported(p->cfg.nm, y)) continue;
       for (int x : widths) {
@@ -1270,7 +1286,7 @@ int cola_autotune(cola_plan p, const cola_particles* q, void* ws_, size_t ws_byt
         float t_min = 1e30f;
         for (int rep = 0; rep < 3 && rc == COLA_OK; ++rep) {
           rc = hip_status(hipEventRecord(e0, st));
-          if (rc == COLA_OK) rc = pm_mesh(p, q->s, p->table[0].a, ws, bin_buffers(p, ws), st);
+          if (rc == COLA_OK) rc = evaluate();
           if (rc == COLA_OK) rc = hip_status(hipEventRecord(e1, st));
           if (rc == COLA_OK) rc = hip_status(hipEventSynchronize(e1));
           float ms = 0.f;
