@@ -70,14 +70,14 @@ enum Stage : int {
   kStBinCount = 0, kStBinScan, kStBinScatter, kStDeposit, kStZFwd, kStYFwd, kStXPoisson,
   kStYInv, kStZInv, kStGatherKickDrift, kStGatherForce, kStFinish, kStLptZFwd, kStLptYFwd, kStLptX,
   kStLptYInv, kStLptZInv, kStLptHessian, kStNoise, kStFft, kStAdjKick, kStAdjDeposit, kStAdjFft, kStAdjGather,
-  kStAdjLpt, kStCheckpoint, kStRunStep, kStUnsort, kStYInvPair, kStAnalysis, kStWriteback, kNumStages
+  kStAdjLpt, kStCheckpoint, kStRunStep, kStUnsort, kStYInvPair, kStAnalysis, kNumStages
 };
 const char* const kStageNames[kNumStages] = {
   "bin_count", "bin_scan", "bin_scatter", "deposit", "fft_z_fwd", "fft_y_fwd",
   "fft_x_poisson", "fft_y_inv", "fft_z_inv", "gather_kick_drift", "gather_force", "gather_finish",
   "lpt_fft_z_fwd", "lpt_fft_y_fwd", "lpt_fft_x_mul", "lpt_fft_y_inv", "lpt_fft_z_inv", "lpt_hessian", "noise",
   "fft_test", "adj_kick_drift", "adj_deposit", "adj_fft", "adj_gather", "adj_lpt", "checkpoint", "run_step", "unsort",
-  "fft_y_inv_pair", "analysis", "writeback"};
+  "fft_y_inv_pair", "analysis"};
 
 // Trace levels: 1 records an event pair around every kernel launch, 2 only around
 // each whole COLA step of cola_run (stage run_step), so step times carry no
@@ -450,7 +450,7 @@ bool resident_pays(cola_plan p) { return p->cfg.np <= (p->cfg.nm > p->cfg.np ? 1
 bool resident_ready(cola_plan p, int i, const cola_particles* q, const float* ws) {
   const auto& r = p->res;
   return r.valid && r.ws == ws && r.s == q->s && r.v == q->v && r.s1 == q->s1 && r.s2 == q->s2 && r.next == i &&
-         (r.gen == p->ws_gen || r.gen + 1 == p->ws_gen);
+         r.gen + 1 == p->ws_gen;
 }
 
 // The PM force at a of the particles at q + s into f.  binned: bb already holds their tile

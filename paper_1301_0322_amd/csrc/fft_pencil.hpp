@@ -313,7 +313,8 @@ struct Pencil {
   // B-layout (positions j2 + R2 j1) -> A-layout (positions b2 + R1 b1), sign S.
   // Destroys q.  Same LDS contract as fwd_like.
   template <int S, int TWS>
-  __device__ static void inv_like(float2 (&q)[UB][R1], float2 (&a)[R2], Ex* ex, const float2* tab) {
+  __device__ static void inv_like(float2 (&q)[UB][R1], float2 (&a)[R2], float2* ex, const float2* tab) {
+    static_assert(!SPLIT, "only the A to B direction is split");
 #pragma unroll
     for (int u = 0; u < UB; ++u) {
       int b, j2;
@@ -338,28 +339,6 @@ struct Pencil {
         for (int jj = 0; jj < R1; ++jj)
           if (u * R1 + jj < R2) a[u * R1 + jj] = ex[b2 * PC + jj * NT + b];
       }
-    } else if constexpr (SPLIT) {
-#pragma unroll
-      for (int u = 0; u < UB; ++u) {
-        int bu, j2;
-        if (!b_unit(u, bu, j2)) continue;
-#pragma unroll
-        for (int k = 0; k < R1; ++k) ex[addr_i(bu, j2, k)] = q[u][k].x;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int j2 = 0; j2 < R2; ++j2) a[j2].x = ex[addr_i(b, j2, b2)];
-      __syncthreads();
-#pragma unroll
-      for (int u = 0; u < UB; ++u) {
-        int bu, j2;
-        if (!b_unit(u, bu, j2)) continue;
-#pragma unroll
-        for (int k = 0; k < R1; ++k) ex[addr_i(bu, j2, k)] = q[u][k].y;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int j2 = 0; j2 < R2; ++j2) a[j2].y = ex[addr_i(b, j2, b2)];
     } else {
 #pragma unroll
       for (int u = 0; u < UB; ++u) {

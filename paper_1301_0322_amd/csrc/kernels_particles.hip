@@ -1295,10 +1295,9 @@ static void gather_sorted_tz(Lattice lat, Bins b, SortedState src, SortedState d
 hipError_t launch_gather_sorted(Lattice lat, Bins b, SortedState src, SortedState dst, BinBuffers bb, int mode,
                                 GatherArgs a, KickArgs k, hipStream_t st) {
   if (mode != kGatherKickDrift && mode != kGatherFinish) return hipErrorInvalidValue;
-  if (!dst.s || !dst.lag || reinterpret_cast<uintptr_t>(dst.s) % 16 != 0) {
-    // dst is packed: 12 n floats from dst.s, 16-byte aligned, and n ints of lag
-    return hipErrorInvalidValue;
-  }
+  // dst is 16-byte aligned: 12 n packed floats and n ints of lag, or for the finish 6 n floats
+  if (!dst.s || reinterpret_cast<uintptr_t>(dst.s) % 16 != 0) return hipErrorInvalidValue;
+  if (mode == kGatherKickDrift && !dst.lag) return hipErrorInvalidValue;
   if (src.lag && reinterpret_cast<uintptr_t>(src.s) % 16 != 0) return hipErrorInvalidValue;
   COLA_TZ_DISPATCH(b.tz, gather_sorted_tz<TZ>(lat, b, src, dst, bb, mode, a, k, st));
   return hipGetLastError();
