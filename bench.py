@@ -68,6 +68,32 @@ def stage_bytes(np_side: int, nm: int) -> dict:
     }
 
 
+def run_stage_bytes(np_side: int, nm: int, lagrangian: bool) -> dict:
+    """Algorithmic HBM bytes per launch of each stage of cola_run, mean over the stage's
+    launches in a step, for the launches that this mesh size and this form of the steps
+    (Plan.get_run_form) make."""
+    sb = stage_bytes(np_side, nm)
+    R = nm**3
+    P = np_side**3
+    if nm <= 256:      # one launch for the three y passes and one for the three z passes
+        sb["fft_y_inv_pair"] += sb.pop("fft_y_inv")
+        sb["fft_z_inv"] *= 3
+    else:              # three z passes in two launches
+        sb["fft_z_inv"] = 3 * sb["fft_z_inv"] // 2
+    sb["bin_count"] = 12 * P + 8 * P               # s -> key and rank
+    if lagrangian:     # 16-byte tile-sorted positions and forces, a streaming kick
+        sb["bin_scatter"] = 8 * P + 12 * P + 16 * P
+        sb["deposit"] = 16 * P + 4 * R
+        sb["gather_force"] = 12 * R + 16 * P + 16 * P
+        sb["gather_kick_drift"] = 16 * P + 48 * P + 24 * P
+        sb["gather_finish"] = 16 * P + 48 * P + 36 * P
+    else:              # the finishing gather writes s and v in order for the unsort pass
+        sb["bin_scatter"] = 8 * P + 4 * P
+        sb["gather_finish"] = 12 * R + 48 * P + 24 * P
+        sb["unsort"] = 24 * P + 24 * P + 48 * P
+    return sb
+
+
 def b_alg_step(np_side: int, nm: int) -> int:
     """Bytes one PM step must move with this pass structure: deposit, z and y forward,
     the x pass (2 outputs), the y passes (x component; Phi -> y, z components), three z
@@ -571,8 +597,8 @@ def main() -> int:
 
     # the same step through the public cola_step call, median over steps 1..n-1: plain
     # (the caller's Lagrangian-order arrays binned from scratch each call) and with
-    # resident steps (each call continues from the particles and bins the previous one
-    # left in the workspace)
+    # resident steps (up to np = 128, or 96 with nm = np, each call continues from the
+    # particles and bins the previous one left in the workspace; above, the plain step)
     def public_steps(resident):
         plan.set_resident_steps(resident)
         plan.init_2lpt(w, p, ws)
@@ -599,7 +625,7 @@ def main() -> int:
     api_step_ms, api_stages = public_steps(0)
     res_step_ms, res_stages = public_steps(1)
 
-    sb = stage_bytes(np_side, nm)
+    sb = run_stage_bytes(np_side, nm, plan.get_run_form() == 1)
     per_run = {k: {"ms": ms / args.steps, "launches": n // args.steps, "ms_per_launch": ms / n}
                for k, (ms, n) in stages.items()}
     dom = max(stages, key=lambda k: stages[k][0])
@@ -652,9 +678,10 @@ def main() -> int:
                     "cola_step_call_resident": {
                         "ms": res_step_ms, "particle_steps_per_s": np_side**3 / (res_step_ms * 1e-3),
                         "hbm_frac": b_alg / (res_step_ms * 1e-3) / (HBM_PEAK_GBS * 1e9),
-                        "timed": "the public cola_step call with resident steps on (each call continues from the "
-                                 "particles and bins the previous call left in the workspace and writes s, v to the "
-                                 "caller's arrays), HIP events around each call, median over steps 1.."
+                        "timed": "the public cola_step call with resident steps on (up to np = 128, or 96 with "
+                                 "nm = np, each call continues from the particles and bins the previous call left "
+                                 "in the workspace; larger sets make the plain step), HIP events around each call, "
+                                 "median over steps 1.."
                                  f"{cfg.n_steps - 1} after cola_init_2lpt",
                         "stages_ms_per_call": res_stages}},
         "stages_per_run": per_run,
