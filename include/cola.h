@@ -110,7 +110,7 @@ int cola_plan_destroy(cola_plan plan);
 
 /* Bytes of workspace every call below needs: four nm^3 float meshes, the
  * per-step particle binning buffers (12 bytes per particle, three int arrays of
- * one entry per 8x8xtz tile, the halo faces of every tile) and two tile-sorted
+ * eight entries per 8x8xtz tile, the scan sums and the crowded-tile list) and two tile-sorted
  * copies of the particle state (104 bytes per particle) used by cola_run and, for sorted
  * positions and forces, by the calls on the caller's arrays. */
 int cola_workspace_bytes(cola_plan plan, size_t *bytes);
@@ -186,11 +186,12 @@ int cola_pm_force(cola_plan plan, const float *s, double a, float *acc, void *ws
  * starts from the state that call left in ws. */
 int cola_step(cola_plan plan, int32_t i, const cola_particles *p, void *ws, void *stream);
 
-/* Resident steps (off by default), for small particle sets, where they save a pass and two
- * launches a step (1 to 5%).  With on = 1 and np <= 128 (np <= 96 when nm = np), cola_step
- * leaves in ws a copy of the updated particle arrays and their tile bins for the next step,
- * and still writes s and v to the caller's arrays.  Larger sets would lose by the copy:
- * their steps leave nothing behind and equal those with on = 0.  The next cola_step (or cola_finish) of this plan continues from
+/* Resident steps (off by default), which save a pass and two launches a step (up to 5%).
+ * With on = 1, cola_step leaves in ws a copy of the updated particle arrays and their tile
+ * bins for the next step, and still writes s and v to the caller's arrays, where that is
+ * faster: for nm >= 3 np, for nm = 2 np with np <= 128 or box < 0.5 np, and for nm = np
+ * with np <= 96, or np <= 192 and box < 0.4 np.  Other plans would lose by the copy: their
+ * steps leave nothing behind and equal those with on = 0.  The next cola_step (or cola_finish) of this plan continues from
  * them, skipping the binning of the caller's arrays, when it is called with step index
  * i + 1 (n_steps for cola_finish), the same particle arrays and the same ws, and no
  * other call of this library has used ws in between; in every other case it starts

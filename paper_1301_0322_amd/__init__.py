@@ -336,8 +336,8 @@ class Plan:
     def set_resident_steps(self, on: int):
         """Resident steps: consecutive step() calls on the same particles and workspace keep
         the particles and their tile bins in the workspace (the arrays must not be changed
-        between them), where that is faster: up to np = 128, or 96 with nm = np; larger sets
-        step as with 0.  0 off (default), 1 on."""
+        between them), where that is faster: fine meshes, small or closely spaced sets (the
+        rule is in cola.h); other plans step as with 0.  0 off (default), 1 on."""
         _check("cola_plan_set_resident_steps", lib().cola_plan_set_resident_steps(self._c, on))
 
     def set_fft_rotation(self, on: int):

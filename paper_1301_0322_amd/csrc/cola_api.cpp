@@ -436,16 +436,26 @@ KickArgs finish_kick(cola_plan p, const StepRow& row) {
 // to the caller's arrays in either case, which are therefore current after every step.
 //
 // Whether a resident step leaves anything behind.  The copy writes 24 bytes a particle at
-// every step and the counting kick saves 12 bytes, two launches and a pass; small sets gain
-// by it and large ones lose, most where a tile holds most particles (np = nm).  A resident
-// step over a plain one at particle spacings of 0.3 and 1.5 Mpc/h (ms a plain step at 0.3):
-//   np = nm:  32 .97 .96 (0.069)  64 1.00 .99 (0.15)  96 .99 .98 (0.21)  128 1.00 1.06 (0.34)
-//            192 1.00 1.06 (0.97)  256 1.02 1.04 (1.51)  512 1.04 (9.9)
-//   nm = 2 np: 32 .97 .96 (0.060)  64 1.00 .97 (0.15)  96 .99 .98 (0.26)  128 .98 1.01 (0.44)
-//            192 .99 1.01 (1.59)  256 1.00 1.02 (3.43)  384 1.00 1.02 (12.5)  512 1.00 1.01 (29.3)
-//   nm = 3 np: 32 .96 .96  64 1.00 .99  128 .99 .99 (1.18)  256 1.00 1.00 (10.2)
-//   nm = 4 np: 96 1.00 1.00  128 1.00 1.00 (2.51)  192 1.00 1.00  256 .99 1.00 (22.4)
-bool resident_pays(cola_plan p) { return p->cfg.np <= (p->cfg.nm > p->cfg.np ? 128 : 96); }
+// every step; the counting kick saves 12 bytes, two launches and a pass whose atomics cost
+// most in crowded sets.  So small sets gain, and larger ones where the particle spacing is
+// fine (crowded late steps) or the mesh passes outweigh both.  Time of initial conditions,
+// ten resident steps and the finish over the same with plain steps, at particle spacings of
+// 0.2, 0.4, 0.55, 0.75 and 1 Mpc/h (two runs of one form differ by 0.1 to 0.3%):
+//   np = nm:    96 .987 .979 .976 .975 .975     128 .984 .979 .991 1.006 1.025
+//              192 .974 .998 1.010 1.031 1.032  256 .998 1.015 1.017 1.016 1.023
+//   nm = 2 np: 128 .975 .977 .983 .982 .988     192 .983 .994 .996 .998 1.002
+//              256 .986 .997 1.000 1.005 1.008  384 .991 .997 1.000 1.004 1.008
+//              512 .991 .998 1.003 1.004 1.007
+//   nm = 3 np: 256 .994 .995 .996 .998 .999
+//   nm = 4 np: 192 .997 .997 .998 .998 .999     256 .995 .996 .995 .998 .997
+// and np from 16 to 64 on every mesh .94 to 1.00 (steps alone).
+bool resident_pays(cola_plan p) {
+  const int np = p->cfg.np, nm = p->cfg.nm;
+  const double spacing = p->cfg.box / np;
+  if (nm >= 3 * np) return true;
+  if (nm == np) return np <= 96 || (np <= 192 && spacing < 0.4);
+  return np <= 128 || spacing < 0.5;
+}
 
 bool resident_ready(cola_plan p, int i, const cola_particles* q, const float* ws) {
   const auto& r = p->res;

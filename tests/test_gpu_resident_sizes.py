@@ -1,7 +1,8 @@
-"""Resident steps keep a copy and bins only where that is faster than a plain step (np up to
-128, or 96 with nm = np): beyond, every step bins the caller's arrays and a resident call
-makes the plain call's launches.  Results equal the plain steps' bit for bit on both sides
-of the line."""
+"""Resident steps keep a copy and bins only where that is faster than a plain step (nm >= 3 np;
+nm = 2 np up to np = 128 or below 0.5 Mpc/h of particle spacing; nm = np up to 96, or up to
+192 below 0.4): elsewhere every step bins the caller's arrays and a resident call makes the
+plain call's launches.  Results equal the plain steps' bit for bit on both sides of the
+lines."""
 import pytest
 import torch
 
@@ -11,11 +12,12 @@ from gpu_util import announce
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("np_side,nm,kept", [
-    (32, 32, True), (96, 96, True), (128, 128, False), (128, 256, True), (192, 384, False), (256, 256, False)])
-def test_resident_steps_keep_state_where_it_pays(np_side, nm, kept):
-    announce(f"resident steps at {np_side}/{nm}")
-    cfg = cola.Config(np=np_side, nm=nm, box=0.5 * np_side, n_steps=3)
+@pytest.mark.parametrize("np_side,nm,spacing,kept", [
+    (32, 32, 2.0, True), (96, 96, 1.0, True), (128, 128, 0.3, True), (128, 128, 0.8, False), (128, 256, 1.0, True),
+    (192, 384, 0.4, True), (192, 384, 1.0, False), (256, 256, 0.3, False), (128, 384, 2.0, True)])
+def test_resident_steps_keep_state_where_it_pays(np_side, nm, spacing, kept):
+    announce(f"resident steps at {np_side}/{nm}, spacing {spacing}")
+    cfg = cola.Config(np=np_side, nm=nm, box=spacing * np_side, n_steps=3)
     w = torch.randn(np_side**3, generator=torch.Generator().manual_seed(nm)).cuda()
     out, counted = {}, {}
     with cola.Plan(cfg) as plan:
