@@ -507,6 +507,8 @@ def main() -> int:
                          "(default: the plan's defaults, the configuration the committed profiles cover)")
     ap.add_argument("--no-autotune", action="store_true", help="the default; kept for older command lines")
     ap.add_argument("--no-paper-mesh", action="store_true", help="skip the 256^3 / 768^3 and 512^3 / 1024^3 PM steps")
+    ap.add_argument("--no-steps", action="store_true",
+                    help="skip timing the public cola_step calls (profiles of the run's launches alone)")
     ap.add_argument("--no-analysis", action="store_true", help="skip timing cola_cross_power")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="also copy 256 MiB device to device once (a known-size kernel for HBM byte counters)")
@@ -597,8 +599,8 @@ def main() -> int:
 
     # the same step through the public cola_step call, median over steps 1..n-1: plain
     # (the caller's Lagrangian-order arrays binned from scratch each call) and with
-    # resident steps (up to np = 128, or 96 with nm = np, each call continues from the
-    # particles and bins the previous one left in the workspace; above, the plain step)
+    # resident steps (each call continues from the particles and bins the previous one left
+    # in the workspace, where the plan keeps them)
     def public_steps(resident):
         plan.set_resident_steps(resident)
         plan.init_2lpt(w, p, ws)
@@ -622,8 +624,9 @@ def main() -> int:
         plan.set_resident_steps(0)
         return float(np.median(step_ms)), stages_
 
-    api_step_ms, api_stages = public_steps(0)
-    res_step_ms, res_stages = public_steps(1)
+    if not args.no_steps:
+        api_step_ms, api_stages = public_steps(0)
+        res_step_ms, res_stages = public_steps(1)
 
     sb = run_stage_bytes(np_side, nm, plan.get_run_form() == 1)
     per_run = {k: {"ms": ms / args.steps, "launches": n // args.steps, "ms_per_launch": ms / n}
@@ -665,28 +668,25 @@ def main() -> int:
                     "hbm_frac_three_chains": b_alg_three_chains(np_side, nm) / (pm_step_ms * 1e-3)
                     / (HBM_PEAK_GBS * 1e9),
                     "timed": f"each COLA step inside cola_run, HIP events around the step only, "
-                             f"mean of {steps_rec[1]} steps",
-                    "cola_step_call": {
-                        "ms": api_step_ms, "particle_steps_per_s": np_side**3 / (api_step_ms * 1e-3),
-                        "hbm_frac": b_alg / (api_step_ms * 1e-3) / (HBM_PEAK_GBS * 1e9),
-                        "hbm_frac_three_chains": b_alg_three_chains(np_side, nm) / (api_step_ms * 1e-3)
-                        / (HBM_PEAK_GBS * 1e9),
-                        "timed": "the public cola_step call on the caller's Lagrangian-order arrays (bins from "
-                                 "scratch each call), HIP events around each call, median over steps 1.."
-                                 f"{cfg.n_steps - 1} after cola_init_2lpt",
-                        "stages_ms_per_call": api_stages},
-                    "cola_step_call_resident": {
-                        "ms": res_step_ms, "particle_steps_per_s": np_side**3 / (res_step_ms * 1e-3),
-                        "hbm_frac": b_alg / (res_step_ms * 1e-3) / (HBM_PEAK_GBS * 1e9),
-                        "timed": "the public cola_step call with resident steps on (up to np = 128, or 96 with "
-                                 "nm = np, each call continues from the particles and bins the previous call left "
-                                 "in the workspace; larger sets make the plain step), HIP events around each call, "
-                                 "median over steps 1.."
-                                 f"{cfg.n_steps - 1} after cola_init_2lpt",
-                        "stages_ms_per_call": res_stages}},
+                             f"mean of {steps_rec[1]} steps"},
         "stages_per_run": per_run,
         "tuning": tuning,
     }
+    if not args.no_steps:
+        out["pm_step"]["cola_step_call"] = {
+            "ms": api_step_ms, "particle_steps_per_s": np_side**3 / (api_step_ms * 1e-3),
+            "hbm_frac": b_alg / (api_step_ms * 1e-3) / (HBM_PEAK_GBS * 1e9),
+            "hbm_frac_three_chains": b_alg_three_chains(np_side, nm) / (api_step_ms * 1e-3) / (HBM_PEAK_GBS * 1e9),
+            "timed": "the public cola_step call on the caller's Lagrangian-order arrays (bins from scratch each "
+                     f"call), HIP events around each call, median over steps 1..{cfg.n_steps - 1} after cola_init_2lpt",
+            "stages_ms_per_call": api_stages}
+        out["pm_step"]["cola_step_call_resident"] = {
+            "ms": res_step_ms, "particle_steps_per_s": np_side**3 / (res_step_ms * 1e-3),
+            "hbm_frac": b_alg / (res_step_ms * 1e-3) / (HBM_PEAK_GBS * 1e9),
+            "timed": "the public cola_step call with resident steps on (each call continues from the particles and "
+                     "bins the previous call left in the workspace, where the plan keeps them), HIP events around "
+                     f"each call, median over steps 1..{cfg.n_steps - 1} after cola_init_2lpt",
+            "stages_ms_per_call": res_stages}
     # density statistics of Section 3.1 on the final state: the run against itself
     # through cola_cross_power (two deposits, two forward FFTs, shell sums)
     out_stats = torch.zeros((6, nm // 2), dtype=torch.float64, device="cuda")
