@@ -210,7 +210,7 @@ struct GatherArgs {
   float* out_b;     // launch_unsort: v_phys
 };
 // Force gather (cola_pm_force): a.out_a[d n + p] = F_d of particle p of the SoA
-// displacements a.s, through the tile lists of bb.
+// displacements a.s, through the tile lists of bb or, where set, its sorted positions.
 // With out4 the force of particle p goes to out4[p] instead (w = 0).
 hipError_t launch_gather_force(Lattice lat, Bins b, BinBuffers bb, GatherArgs a, hipStream_t st,
                                float4* out4 = nullptr);
@@ -228,9 +228,9 @@ struct SortedState {
   int* lag;
 };
 // Gather + kick over the tile lists bb.idx (slots of src).  kGatherKickDrift writes
-// the kicked and drifted record of list position j to slot j of the packed dst
-// (ordered by this step's tiles) and bins it for the next step (bb.count_next,
-// bb.key_rank by dst slot); kGatherFinish writes s and the kicked v in Lagrangian order, as
+// the kicked and drifted record of list position j to the packed dst (ordered by this
+// step's tiles; the records of a wave are grouped by the tile they move to within the
+// wave's slots) and bins it for the next step (bb.count_next, bb.key_rank by dst slot); kGatherFinish writes s and the kicked v in Lagrangian order, as
 // float4 p of dst.s (s.x s.y s.z v.x) and float2 p of dst.s + 4n (v.y v.z), for
 // launch_unsort.
 hipError_t launch_gather_sorted(Lattice lat, Bins b, SortedState src, SortedState dst, BinBuffers bb, int mode,

@@ -47,7 +47,8 @@ __global__ __launch_bounds__(kPartThreads) void k_fill(float4* p, long n4, float
 //               particles with its key (lanes sharing a key take one atomic);
 //   bin_scan    exclusive prefix sum of the key counts (tile t owns the particle
 //               range [offset[8t], offset[8t + 8]));
-//   bin_scatter idx[offset[key] + rank] = slot;
+//   bin_scatter idx[offset[key] + rank] = slot, or the particle's position and
+//               Lagrangian index themselves there (k_bin_scatter_pos);
 //   deposit     per tile: its own particles plus the boundary classes of its seven
 //               lower neighbours that reach into it, accumulated in an LDS tile of
 //               exactly the tile's cells, which are then written with plain stores:
@@ -153,12 +154,14 @@ __device__ __forceinline__ int key_of(const Bins& b, const int c[3]) {
   return tile * kClasses + class_position(cls);
 }
 
-// Rank of each active lane among the lanes of its wave with the same bin, plus one
-// atomic per distinct bin that reserves the ranks.  Called by every lane of the wave.
-// The ballot loop only groups the lanes; the group leaders then issue their atomics
-// together, so a wave waits for one atomic round trip whatever its number of bins.  The
-// bin of a round is read from its lane by v_readlane (the lane is wave-uniform), not by a
-// shuffle through the LDS unit: binning 256^3 particles 0.121 -> 0.110 ms.
+// The rank of a particle in its bin: the lanes of a wave with the same bin form a group
+// (wave_group), whose leader reserves ranks for all of them with one atomic
+// (wave_reserve); a lane's rank is its place in the group after the reserved base
+// (wave_settle).  All three are called by every lane of the wave.  The ballot loop only
+// groups the lanes; the leaders then issue their atomics together, so a wave waits for one
+// atomic round trip whatever its number of bins.  The bin of a round is read from its lane
+// by v_readlane (the lane is wave-uniform), not by a shuffle through the LDS unit: binning
+// 256^3 particles 0.121 -> 0.110 ms.
 struct WaveGroup {
   int leader;    // the lane that reserves for this lane's group
   int below;     // lanes of the group before this one
@@ -192,7 +195,10 @@ __device__ __forceinline__ int wave_settle(int base, const WaveGroup& g) { retur
 // the lattice 0.109 -> 0.093 ms with four, the scatter in a run 0.060 -> 0.047 ms.  The
 // counting blocks of one XCD take one contiguous range of particles, so that a tile's
 // counters are shared by fewer XCDs: a clustered set 0.169 -> 0.139 ms (the scatters, which
-// have no atomics, measured slower that way and keep the plain order).
+// have no atomics, measured slower that way and keep the plain order).  np^3 of every
+// supported size is a whole number of blocks in its form (256 particles below 2^20, 1024
+// from there on); only the grid, rounded up to eight blocks, has empty ones, so the clamps
+// of single lanes are defensive.
 constexpr int kBinPer = 4;
 
 template <int TZ, int U>
@@ -467,7 +473,7 @@ __device__ __forceinline__ bool local_stencil(const Lattice& lat, const TileGeom
 // at 48 KB (three blocks per CU at depth 64) and reads each mesh cell from HBM once.
 // The rows are not padded: particles read them at random cells, so a pad buys no bank
 // freedom, and unpadded rows take one 16-byte LDS store per four cells instead of four
-// 4-byte ones (with the scalar lane reads of wave_rank, the in-run gather of 256^3
+// 4-byte ones (with the scalar lane reads of wave_group, the in-run gather of 256^3
 // particles on 512^3 cells went from 0.955 to 0.937 ms) and the four-field tile of the
 // adjoint gather fits five times in a CU instead of four.
 // Every load of a lane is issued before its first LDS write, so a block has all of
@@ -977,8 +983,9 @@ __device__ __forceinline__ void load_record(const SortedState& st, long n, int j
   }
 }
 
-// wave_rank, and the position of each lane in the wave's order grouped by tile and then
-// by key (pos): the lanes of one tile take consecutive positions, so that the next step's
+// The rank of each active lane's particle (wave_group, wave_reserve and wave_settle in one
+// pass), and the position of the lane in the wave's order grouped by tile and then by key
+// (pos): the lanes of one tile take consecutive positions, so that the next step's
 // reader of a tile finds the records that came from here in runs.  Up to half of the
 // particles change tile in a step, and each one read out of order costs a line per plane;
 // the grouping comes out of rounds the rank needs anyway.  256^3 particles, 512^3 cells:
@@ -1303,13 +1310,8 @@ hipError_t launch_gather_sorted(Lattice lat, Bins b, SortedState src, SortedStat
   return hipGetLastError();
 }
 
-// The closing gather's output (s and v of every particle in Lagrangian order) into the
-// caller's arrays, with L+(a_n) (eq. Lops): v_phys = v + T[D1] s1 + T[D2] s2 (k.td1, k.td2;
-// s1, s2 from the caller's arrays) and x = (q + s) mod L; every access in order.  The gather
-// scatters 24 bytes a particle so that this pass need not collect them through a
-// permutation: 256^3 particles, gather 0.93 -> 1.13 ms, this 0.61 -> 0.28 (512^3: 6.9 -> 8.3
-// and 4.8 -> 2.25; one 32-byte record a particle instead of two planes: 0.30 here).
-// Component d of the outputs of particle p: x = (q + s) mod L and v_phys (eq. Lops).
+// Component d of the outputs of particle p: x = (q + s) mod L and v_phys = v + T[D1] s1 +
+// T[D2] s2 (k.td1, k.td2), the L+(a_n) of the closing step (eq. Lops).
 __device__ __forceinline__ void closing_outputs(const Lattice& lat, const GatherArgs& g, const KickArgs& k, long p,
                                                 int d, int li, float s, float v, float s1, float s2) {
   g.out_b[d * lat.npart + p] = v + k.td1 * s1 + k.td2 * s2;
@@ -1319,6 +1321,12 @@ __device__ __forceinline__ void closing_outputs(const Lattice& lat, const Gather
   g.out_a[d * lat.npart + p] = x;
 }
 
+// The closing gather's output (s and v of every particle in Lagrangian order) into the
+// caller's arrays, with closing_outputs (s1, s2 from the caller's arrays); every access in
+// order.  The gather scatters 24 bytes a particle so that this pass need not collect them
+// through a permutation: 256^3 particles, gather 0.93 -> 1.13 ms, this 0.61 -> 0.28 (512^3:
+// 6.9 -> 8.3 and 4.8 -> 2.25; one 32-byte record a particle instead of two planes: 0.30
+// here).
 __global__ __launch_bounds__(kPartThreads) void k_unsort(Lattice lat, SortedState w, GatherArgs g, KickArgs k) {
   const long n = lat.npart;
   const long p = (long)blockIdx.x * kPartThreads + threadIdx.x;

@@ -1,6 +1,7 @@
 """The binning passes with four particles per thread (2^20 particles and more) and with
-one (below), with a partial last block: the density equals the oracle's, and the mass
-deposit of both forms is exact in sum."""
+one (below), with the empty blocks that round a grid up to a multiple of eight (24^3: 54
+full blocks of 256, 56 launched; no supported size has a partial block): the density equals
+the oracle's, and the mass deposit of both forms is exact in sum."""
 import numpy as np
 import pytest
 import torch

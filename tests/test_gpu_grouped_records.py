@@ -1,9 +1,10 @@
-"""The in-run gather writes each wave's records grouped by the tile they move to: whole
-runs and resident steps, which read that order, equal the steps that pack the caller's
-arrays afresh bit for bit.  Sizes on both sides of every line where a run steps on tile-sorted copies or
-on the Lagrangian-order arrays; one tile along an axis, tiles with less than a wave,
-with several batches and on the crowded list, and depths that make 256- and 512-thread
-tile blocks."""
+"""Whole runs, resident steps and single steps equal each other bit for bit.  The runs at
+(24, 48), (16, 32), (16, 48), (32, 64), (32, 128), (192, 384) and (384, 768) keep the state
+in tile-sorted copies, whose gather writes each wave's records grouped by the tile they move
+to; the other runs, and all steps, work on Lagrangian-order arrays (both forms at the same
+sizes: test_gpu_run_forms.py).  One tile along an axis, tiles with less than a wave, with
+several batches and on the crowded list, and depths that make 256- and 512-thread tile
+blocks."""
 import pytest
 import torch
 

@@ -1,7 +1,8 @@
 """Steps on Lagrangian-order arrays (tile-sorted positions, forces back in Lagrangian order,
-a streaming kick): one thread and four per scatter block, a grid that is not a multiple of
+a streaming kick): one particle and four per scatter thread, a grid that is not a multiple of
 eight blocks, every bin depth's key, and the variants of the kick, against whole runs bit
-for bit; the checkpoints equal the displacements after each step."""
+for bit (tile-sorted ones at (16, 32) and (32, 128), Lagrangian ones at the other sizes); the
+checkpoints equal the displacements after each step."""
 import pytest
 import torch
 

@@ -1,5 +1,5 @@
-"""Resident steps: consecutive cola_step calls continue from the tile-sorted state and
-bins that the previous call left in the workspace, as cola_run's steps do.
+"""Resident steps: consecutive cola_step calls continue from the copy of the particles and
+the tile bins that the previous call left in the workspace (all plans here keep them).
 
 Every result must equal cola_run's and the plain per-step path's bit for bit (the
 deposit sums 64-bit fixed point and the gathers share their arithmetic), and any other
