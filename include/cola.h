@@ -292,7 +292,7 @@ int cola_plan_get_fft_rotation(cola_plan plan, int32_t *rows);
 /* Form of the steps inside cola_run (a tuning knob; results are identical bit for bit
  * either way).  form = 0 keeps the particle state in two workspace copies sorted by mesh
  * tile, form = 1 steps on the caller's Lagrangian-order arrays with only the positions
- * sorted, form = -1 restores the built-in choice by np, nm and box; other values give
+ * sorted, form = -1 restores the built-in choice by np, nm, box and n_steps; other values give
  * COLA_ERR_INVALID.  cola_step, cola_finish and cola_run_checkpointed always use
  * Lagrangian-order steps.  Host-only. */
 int cola_plan_set_run_form(cola_plan plan, int32_t form);

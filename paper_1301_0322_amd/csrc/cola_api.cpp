@@ -544,12 +544,21 @@ int lagrangian_finish(cola_plan p, const SortedState& src, const cola_particles*
 // or on the tile-sorted copies.  The sorted form moves 152 bytes a particle and step (scan
 // lists, deposit, gather), most of them as 52-byte records read out of order; the other one
 // moves 180, but only 16-byte positions and forces out of order.  So the second wins where
-// the order counts, in small sets and in crowded ones (the finer the particle spacing, the
-// more crowded a run gets), and the first in large, even ones.  Time of the Lagrangian run
-// over the sorted one, 10 steps to z = 0, at particle spacings of 0.2, 0.5 (np = nm: 0.4), 1
-// and 2 Mpc/h (two runs of one form differ by 0.2-0.5%, below np = 48 by up to 3%):
-//   np = nm:  64  .78 .80 .84 .89    128  .71 .79 .88 .96    192  .78 .83 1.00 1.03
-//            256  .90 .99 1.06 1.07  384  1.02 1.06 1.10 1.10
+// the order counts: in small sets, in crowded ones (the finer the particle spacing, the more
+// crowded a run gets), and where particles move far in a step, so that a record's neighbours
+// have moved elsewhere (few steps, fine spacing); the first in large, even ones.
+// With nm = np, where a tile holds most particles, the line is a bound on np^3 n_steps
+// box / np.  Time of the Lagrangian run over the sorted one at particle spacings of 0.2, 0.4,
+// 0.7, 1.2 and 2 Mpc/h (two runs of one form differ by 0.2-0.5%), to z = 0:
+//   192: 3 steps .78 .83 .90 .94 .97    5 .79 .83 .92 .98 .99      7 .78 .82 .94 .99 1.01
+//       10 .78 .83 .95 1.00 1.03       20 .80 .84 .97 1.03 1.05
+//   256: 3 .88 .92 .95 .98 .99          5 .89 .95 .99 1.02 1.03    7 .89 .98 1.02 1.04 1.05
+//       10 .90 .99 1.04 1.06 1.07      20 .91 1.01 1.07 1.10 1.10
+//   384: 3 .90 .94 .98 1.01 1.02        5 .96 1.00 1.03 1.05 1.06  7 .99 1.03 1.06 1.08 1.08
+//       10 1.02 1.06 1.08 1.10 1.10    20 1.05 1.12 1.13 1.14 1.14
+//   512: 3 .92 .96 .99 1.01 1.02        5 .99 1.02 1.04 1.06 1.07  7 1.03 ... 1.09
+// and 0.71 to 0.96 up to np = 128 (10 steps).  On finer meshes, 10 steps at 0.2, 0.5, 1 and
+// 2 Mpc/h (below np = 48 two runs of one form differ by up to 3%):
 //   nm = 2 np: 32 .86 .95 .96 .98 (3.1 Mpc/h: 1.01)  48  .80 .90 .96 1.02   64  .85 .87 .94 1.00
 //             96  .86 .92 1.00 1.01  128  .81 .94 .96 .99    192  .97 1.01 1.02 1.02
 //            256  1.01 1.04 1.05 1.04
@@ -562,7 +571,7 @@ int lagrangian_finish(cola_plan p, const SortedState& src, const cola_particles*
 bool lagrangian_run(cola_plan p) {
   if (p->run_form >= 0) return p->run_form == 1;
   const int np = p->cfg.np, nm = p->cfg.nm;
-  if (nm == np) return np <= 192 || (np == 256 && p->cfg.box < 0.4 * np);
+  if (nm == np) return np <= 128 || (double)cube(np) * p->cfg.n_steps * p->cfg.box / np < 9e7;
   return np > 32 && np <= 128;
 }
 

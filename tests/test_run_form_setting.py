@@ -21,10 +21,12 @@ def test_run_form_setting():
 
 
 # sizes where the measured times of the two forms differ by 3% and more
-@pytest.mark.parametrize("np_side,nm,spacing,form", [
-    (32, 32, 1.0, 1), (128, 128, 0.5, 1), (192, 192, 0.3, 1), (256, 256, 0.2, 1), (256, 256, 1.0, 0),
-    (256, 256, 2.0, 0), (384, 384, 0.5, 0), (384, 384, 2.0, 0), (512, 512, 0.3, 0), (32, 96, 2.0, 0),
-    (48, 96, 0.5, 1), (64, 192, 0.2, 1), (64, 256, 0.5, 1), (128, 256, 0.8, 1), (256, 512, 0.5, 0)])
-def test_default_form_is_the_faster_one(np_side, nm, spacing, form):
-    with cola.Plan(cola.Config(np=np_side, nm=nm, box=spacing * np_side)) as p:
+@pytest.mark.parametrize("np_side,nm,n_steps,spacing,form", [
+    (32, 32, 10, 1.0, 1), (128, 128, 10, 0.5, 1), (192, 192, 10, 0.3, 1), (192, 192, 20, 2.0, 0),
+    (256, 256, 10, 0.2, 1), (256, 256, 3, 0.7, 1), (256, 256, 5, 0.4, 1), (256, 256, 10, 1.0, 0),
+    (256, 256, 7, 2.0, 0), (384, 384, 3, 0.2, 1), (384, 384, 10, 0.5, 0), (384, 384, 5, 2.0, 0),
+    (512, 512, 10, 0.3, 0), (512, 512, 3, 0.2, 1), (32, 96, 10, 2.0, 0), (48, 96, 10, 0.5, 1), (64, 192, 10, 0.2, 1),
+    (64, 256, 10, 0.5, 1), (128, 256, 10, 0.8, 1), (256, 512, 10, 0.5, 0)])
+def test_default_form_is_the_faster_one(np_side, nm, n_steps, spacing, form):
+    with cola.Plan(cola.Config(np=np_side, nm=nm, box=spacing * np_side, n_steps=n_steps)) as p:
         assert p.get_run_form() == form
